@@ -268,18 +268,46 @@ __global__ __launch_bounds__(256, 3) void k_proj_dot_mfma_pair(const double2 *__
         }
 }
 
-// C[j][i] = sum_c part[c][j][i]  (fixed order)
-__global__ void k_proj_reduce(const double2 *__restrict__ part, int nchunk, int nl, double2 *__restrict__ C)
+// C[e] = sum_c part[c][e], e = (j, i), added in the order of the K-chunks.  A workgroup of 256 threads
+// owns kRedE consecutive e: all threads fetch the partials of 256 chunks into LDS (16 consecutive e are
+// 256 bytes of a row of part), then thread (e, component) adds them in order from there, while the next
+// 256 are on their way.  One thread per e, walking memory by itself, waits for a load every few
+// additions and leaves all but a few CUs idle.
+constexpr int kRedE = 4, kRedC = 256;   // a row of partials in LDS is padded by one element
+__global__ __launch_bounds__(256) void k_proj_reduce(const double2 *__restrict__ part, int nchunk, int nl,
+                                                     double2 *__restrict__ C)
 {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= nl) return;
-    double r = 0, im = 0;
-    for (int c = 0; c < nchunk; ++c) {
-        double2 v = part[(long)c * nl + e];
-        r += v.x;
-        im += v.y;
+    __shared__ double sh[2][kRedE][2][kRedC + 1];
+    const int q = (int)threadIdx.x, ei = q % kRedE, c0 = q / kRedE;
+    const int e = blockIdx.x * kRedE + ei;
+    constexpr int RPT = kRedC * kRedE / 256;   // partials a thread fetches per slice
+    auto fetch = [&](int s, double2 (&v)[RPT]) {
+#pragma unroll
+        for (int r = 0; r < RPT; ++r) {
+            const int c = s + c0 + r * (256 / kRedE);
+            v[r] = (e < nl && c < nchunk) ? part[(long)c * nl + e] : make_double2(0.0, 0.0);
+        }
+    };
+    double2 v[RPT];
+    fetch(0, v);
+    double sum = 0;
+    const int se = q >> 1, sc = q & 1;   // threads below 2 kRedE add: element, real or imaginary part
+    for (int s = 0, b = 0; s < nchunk; s += kRedC, b ^= 1) {
+#pragma unroll
+        for (int r = 0; r < RPT; ++r) {
+            sh[b][ei][0][c0 + r * (256 / kRedE)] = v[r].x;
+            sh[b][ei][1][c0 + r * (256 / kRedE)] = v[r].y;
+        }
+        __syncthreads();   // the slice before last has been added: its buffer was free
+        if (s + kRedC < nchunk) fetch(s + kRedC, v);
+        if (q < 2 * kRedE) {
+            const int m = nchunk - s < kRedC ? nchunk - s : kRedC;
+#pragma unroll 16
+            for (int c = 0; c < m; ++c) sum += sh[b][se][sc][c];
+        }
     }
-    C[e] = make_double2(r, im);
+    const int eo = blockIdx.x * kRedE + se;
+    if (q < 2 * kRedE && eo < nl) ((double *)(C + eo))[sc] = sum;
 }
 
 // --------------------------------------------------------------- X + V E (MFMA)
@@ -466,7 +494,7 @@ hipError_t launch_proj_dot(const double2 *V, int l, long vstride, const S *X, lo
 #undef OV_DOT_CASE
     }
     const int nl = n * l;
-    hipLaunchKernelGGL(k_proj_reduce, dim3((nl + 255) / 256), dim3(256), 0, st, part, nchunk, nl, C);
+    hipLaunchKernelGGL(k_proj_reduce, dim3((nl + kRedE - 1) / kRedE), dim3(256), 0, st, part, nchunk, nl, C);
     return hipGetLastError();
 }
 
