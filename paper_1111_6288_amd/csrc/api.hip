@@ -120,6 +120,7 @@ struct ov_ctx {
     // dslash launch shape per precision and kind (0: plain, 1: fused Clenshaw epilogue)
     struct Launch {
         int nr = 2, block = 128, order = 0, cap = 0, stream_hint = 0, split = 1, cols = 1, wshare = 1;
+        bool chosen = false;   // set by the caller or the autotuner; otherwise dslash_launch picks per batch
     };
     Launch tune[3][2];
 
@@ -434,6 +435,27 @@ template <>
 const uint32_t *links_of<uint32_t>(const ov_ctx *c) { return c->U16; }
 
 // ---------------------------------------------------------------- launch helpers
+// Kernel of a dslash launch whose shape nobody chose (ov_set_tuning and its
+// relatives, ov_autotune).  Small batches wait for memory latency, not
+// bandwidth, and take the direction-wave kernel: mean of the plain and the
+// fused launch inside a captured graph, FP64 12 RHS of 4^4 16.7 -> 5.2 us,
+// FP32 4 RHS of 8^3x16 16.3 -> 6.7 us (an empty graph node takes 1.6 us).
+// Its four waves hold their own copy of no link, but every right-hand side
+// reads (and rebuilds the third row of) all eight: one vector gains up to the
+// largest lattice (24^3x48 FP64 222 -> 175 us, FP32 96 -> 81), a batch until
+// its fields outgrow the caches and the link sharing of the site-parallel
+// kernels wins (12 RHS: FP64 12^3x24, 96 MB a field batch, 96 us against 100;
+// 16^3x32, 302 MB, 336 against 301).  BF16 halves the bytes but not the
+// arithmetic: 12 RHS of 8^3x16 (4.7 MB) 11.8 against 12.4 us, 4 RHS of
+// 12^3x24 (8 MB) 17.2 against 16.3.
+template <class S>
+bool dir_waves_rule(const Geo &g, int n)
+{
+    const double batch = 12.0 * sizeof(S) * g.V * n;
+    if (sizeof(S) == 4) return batch <= 7e6;
+    return n <= 3 || batch <= 96e6;
+}
+
 template <class S>
 int dslash_launch(ov_ctx *c, const Batch &b, const int *fgroup, const S *x, S *y, double a, bool hw,
                   const S *e1 = nullptr, double c1 = 0, const S *e2 = nullptr, double c2 = 0,
@@ -472,6 +494,20 @@ int dslash_launch(ov_ctx *c, const Batch &b, const int *fgroup, const S *x, S *y
         int nch = (int)std::max(1L, std::min((long)c->g.Lt / 4, (4096 + per_chunk - 1) / per_chunk));
         d.tchunk = (c->g.Lt + nch - 1) / nch;
     }
+    const double sb = sizeof(S);
+    const int nex = (e1 ? 1 : 0) + (e2 ? 1 : 0) + (e3 ? 1 : 0);
+    // compulsory bytes: the links once (two rows of each when rebuilt), every
+    // input and epilogue field once, the output once
+    const double bytes =
+        (double)c->g.V * ((c->recon ? 24.0 : 36.0) * sb + (double)b.n * 12.0 * sb * (2 + nex));
+    if (!tu.chosen && dir_waves_rule<S>(c->g, b.n)) {
+        d.order = 0;
+        d.stream_hint = 0;
+        int pi = prof_begin(c);
+        HIPCHK(launch_dslash_dir<S>(d, hw || epi, epi, c->stream));
+        prof_end(c, pi, epi ? PC_CLENSHAW : PC_DSLASH, bytes);
+        return OV_OK;
+    }
     int nr = tu.nr, split = tu.split, ws = tu.wshare;
     while (split > 1 && (split / 2) * nr >= b.n) split /= 2;
     while (nr > 1 && nr / 2 >= b.n) nr /= 2;
@@ -479,12 +515,7 @@ int dslash_launch(ov_ctx *c, const Batch &b, const int *fgroup, const S *x, S *y
     d.wshare = ws;
     int pi = prof_begin(c);
     HIPCHK(launch_dslash<S>(d, hw || epi, epi, nr, tu.block, split, c->stream));
-    const double sb = sizeof(S);
-    const int nex = (e1 ? 1 : 0) + (e2 ? 1 : 0) + (e3 ? 1 : 0);
-    // compulsory bytes: the links once (two rows of each when rebuilt), every
-    // input and epilogue field once, the output once
-    prof_end(c, pi, epi ? PC_CLENSHAW : PC_DSLASH,
-             (double)c->g.V * ((c->recon ? 24.0 : 36.0) * sb + (double)b.n * 12.0 * sb * (2 + nex)));
+    prof_end(c, pi, epi ? PC_CLENSHAW : PC_DSLASH, bytes);
     return OV_OK;
 }
 
@@ -1451,6 +1482,7 @@ int ov_set_tuning(ov_ctx *c, int prec, int rhs_per_thread, int block)
         tu.block = block;
         tu.wshare = 1;
         if (rhs_per_thread > 2) tu.split = 1;
+        tu.chosen = true;
     }
     return OV_OK;
 }
@@ -1461,7 +1493,10 @@ int ov_set_site_order(ov_ctx *c, int prec, int order)
     CHK(check_prec(c, prec));
     if (order < 0 || order > 3) return fail(c, OV_EINVAL, "site order must be 0, 1, 2 or 3");
     invalidate_graphs(c);
-    for (auto &tu : c->tune[prec]) tu.order = order;
+    for (auto &tu : c->tune[prec]) {
+        tu.order = order;
+        tu.chosen = true;
+    }
     return OV_OK;
 }
 
@@ -1471,7 +1506,10 @@ int ov_set_occupancy(ov_ctx *c, int prec, int blocks_per_cu)
     CHK(check_prec(c, prec));
     if (blocks_per_cu < 0 || blocks_per_cu > 32) return fail(c, OV_EINVAL, "blocks_per_cu outside [0, 32]");
     invalidate_graphs(c);
-    for (auto &tu : c->tune[prec]) tu.cap = blocks_per_cu;
+    for (auto &tu : c->tune[prec]) {
+        tu.cap = blocks_per_cu;
+        tu.chosen = true;
+    }
     return OV_OK;
 }
 
@@ -1523,6 +1561,7 @@ int ov_set_launch_config(ov_ctx *c, int prec, int kind, const int *cfg)
     tu.split = sp;
     tu.cols = cl;
     tu.wshare = ws;
+    tu.chosen = true;
     return OV_OK;
 }
 
@@ -2172,7 +2211,7 @@ int ov_autotune(ov_ctx *c, int prec, int nrhs, const char *cache_path)
         c->prof_on = false;
         const bool slab_ok = c->g.Lz % 8 == 0 && c->g.V % 64 == 0;
         const bool tslab_ok = c->g.Lt % 8 == 0 && c->g.V % 64 == 0;
-        float best_ms[2] = {0, 0};
+        float best_ms[2] = {0, 0}, own_ms[2] = {0, 0};
         int rc = OV_OK;
         for (int kind = 0; kind < 2 && rc == OV_OK; ++kind) {
             auto &tu = c->tune[prec][kind];
@@ -2183,6 +2222,20 @@ int ov_autotune(ov_ctx *c, int prec, int nrhs, const char *cache_path)
             const auto keep = tu;
             auto bestc = tu;
             float best = 1e30f;
+            auto timed = [&](float *ms) -> int {
+                CHK(launch());
+                if (hipEventRecord(e0, c->stream) != hipSuccess) return OV_EHIP;
+                for (int rep = 0; rep < reps; ++rep) CHK(launch());
+                if (hipEventRecord(e9, c->stream) != hipSuccess || hipEventSynchronize(e9) != hipSuccess ||
+                    hipEventElapsedTime(ms, e0, e9) != hipSuccess)
+                    return OV_EHIP;
+                return OV_OK;
+            };
+            // the kernel taken when no shape is chosen; it stays unless a shape beats it
+            tu.chosen = false;
+            float own = 0;
+            rc = timed(&own);
+            tu.chosen = true;
             for (int sh = 0; sh < 2 && rc == OV_OK; ++sh)
             for (int od = 0; od < 4 && rc == OV_OK; ++od)
             for (int cl : colss)
@@ -2213,13 +2266,8 @@ int ov_autotune(ov_ctx *c, int prec, int nrhs, const char *cache_path)
                     tu.split = sp;
                     tu.cols = cl;
                     tu.wshare = ws;
-                    if (rc == OV_OK) rc = launch();
-                    if (rc == OV_OK && hipEventRecord(e0, c->stream) != hipSuccess) rc = OV_EHIP;
-                    for (int rep = 0; rep < reps && rc == OV_OK; ++rep) rc = launch();
-                    if (rc == OV_OK && hipEventRecord(e9, c->stream) != hipSuccess) rc = OV_EHIP;
-                    if (rc == OV_OK && hipEventSynchronize(e9) != hipSuccess) rc = OV_EHIP;
                     float ms = 0;
-                    if (rc == OV_OK && hipEventElapsedTime(&ms, e0, e9) != hipSuccess) rc = OV_EHIP;
+                    if (rc == OV_OK) rc = timed(&ms);
                     if (rc != OV_OK) break;
                     if (ms < best) {
                         best = ms;
@@ -2228,7 +2276,9 @@ int ov_autotune(ov_ctx *c, int prec, int nrhs, const char *cache_path)
                 }
             }
             tu = rc == OV_OK ? bestc : keep;
+            if (rc == OV_OK) tu.chosen = best < own;
             best_ms[kind] = best / (float)reps;
+            own_ms[kind] = own / (float)reps;
         }
         c->prof_on = was;
         invalidate_graphs(c);
@@ -2244,10 +2294,10 @@ int ov_autotune(ov_ctx *c, int prec, int nrhs, const char *cache_path)
                                  "{\"arch\": \"gfx950\", \"L\": [%d, %d, %d, %d], \"prec\": %d, \"nrhs\": %d, "
                                  "\"kind\": \"%s\", \"rhs_per_thread\": %d, \"block\": %d, \"site_order\": %d, "
                                  "\"blocks_per_cu\": %d, \"stream_hint\": %d, \"rhs_split\": %d, \"cols\": %d, "
-                                 "\"wshare\": %d, \"two_row_links\": %d, \"ms_per_launch\": %.6f}\n",
+                                 "\"wshare\": %d, \"two_row_links\": %d, \"ms_per_launch\": %.6f, \"ms_unchosen\": %.6f}\n",
                                  c->L[0], c->L[1], c->L[2], c->L[3], prec, nrhs, kind ? "clenshaw" : "dslash",
                                  tu.nr, tu.block, tu.order, tu.cap, tu.stream_hint, tu.split, tu.cols, tu.wshare,
-                                 c->recon ? 1 : 0, best_ms[kind]);
+                                 c->recon ? 1 : 0, best_ms[kind], own_ms[kind]);
                 }
                 std::fclose(fp);
             }

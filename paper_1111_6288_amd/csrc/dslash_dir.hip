@@ -1,0 +1,290 @@
+// H_w / D_w for small batches: one wave per direction of the stencil.
+//
+// Same operator and epilogue as the site-parallel kernels:
+//   y_r = a * G (D_w x_r)  +  c1 e1_r + c2 e2_r + c3 e3_r          (own site)
+//
+// The four waves of a workgroup cover the same 64 sites of one right-hand
+// side; wave mu gathers the two hops of direction mu and leaves the link times
+// half spinor of each in LDS ([hop][2 x 3 components][lane]), after which wave
+// w sums a quarter of the components, hop by hop in the order of the
+// site-parallel kernels, so the result has the same bits as theirs.
+//
+// What bounds a small batch is memory latency.  The loads of a thread (two
+// links, two neighbours, its share of the own-site operands) depend on nothing
+// but the site index and stand before the arithmetic, without branches between
+// them, so they are all in flight together: the kernel waits for memory about
+// once, where a thread that walks the eight hops one after the other, each
+// behind its boundary branch, waits for the links and the spinor of every hop
+// in turn.  It also has four times the wavefronts for the same sites.
+// Mean of a plain and a fused launch in a captured graph (an empty node takes
+// 1.6 us), site-parallel kernel and this one:
+//   FP64 12 RHS of 4^4 16.7 -> 5.1 us, FP32 4 RHS of 8^3x16 16.3 -> 6.7 us,
+//   FP64 1 RHS of 16^3x32 37.7 -> 31 us, of 24^3x48 222 -> 175 us.
+#include <type_traits>
+
+#include "dslash_device.h"
+#include "ov_internal.h"
+
+namespace ov {
+
+// A unit is the 16-byte element of the storage layout: one FP64 or two FP32
+// components (one of BF16).
+template <class S>
+struct UnitOf {
+    using R = typename StoreT<S>::real;
+    static constexpr int C = Pair<S>::E;      // components per unit
+    static constexpr int N = 12 / C;          // units per spinor
+    struct T {
+        cx<R> c[C];
+    };
+};
+
+// Unit q of a field at one site.
+template <class S, bool NT>
+__device__ __forceinline__ typename UnitOf<S>::T ld_unit(const S *__restrict__ f, int Vp, int q, unsigned site)
+{
+    using R = typename StoreT<S>::real;
+    typename UnitOf<S>::T t;
+    if constexpr (UnitOf<S>::C == 2) {
+        if constexpr (NT) ldpair_nt<S, R>(f, Vp, q, site, t.c[0], t.c[1]);
+        else ldpair<S, R>(f, Vp, q, site, t.c[0], t.c[1]);
+    } else {
+        if constexpr (NT) t.c[0] = ldp_nt<S, R>(f + (size_t)q * (unsigned)Vp, site);
+        else t.c[0] = ldp<S, R>(f + (size_t)q * (unsigned)Vp, site);
+    }
+    return t;
+}
+
+template <class S, bool NT>
+__device__ __forceinline__ void st_unit(S *__restrict__ f, int Vp, int q, unsigned site, const typename UnitOf<S>::T &t)
+{
+    using R = typename StoreT<S>::real;
+    if constexpr (UnitOf<S>::C == 2) {
+        if constexpr (NT) stpair_nt<S, R>(f, Vp, q, site, t.c[0], t.c[1]);
+        else stpair<S, R>(f, Vp, q, site, t.c[0], t.c[1]);
+    } else {
+        if constexpr (NT) stp_nt<S, R>(f + (size_t)q * (unsigned)Vp, site, t.c[0]);
+        else stp<S, R>(f + (size_t)q * (unsigned)Vp, site, t.c[0]);
+    }
+}
+
+// Both hops of direction MU at `site` (a real site): link times half spinor
+// to out[6 components at stride 64], the forward hop first, the backward hop
+// 6 x 64 behind.  A hop that leaves the lattice through a Dirichlet boundary
+// reads the wrapped site like any other and its half spinor is replaced by
+// zeros (not multiplied: the neighbour may hold infinities or NaN).
+template <int MU, class S, bool REC>
+__device__ __forceinline__ void dir_hops(const DsArgs<S> &a, const S *__restrict__ x, int site, int cmu, int Lmu,
+                                         int stride, cx<typename StoreT<S>::real> ph,
+                                         cx<typename StoreT<S>::real> *__restrict__ out)
+{
+    using R = typename StoreT<S>::real;
+    const int Vp = a.g.Vp;
+    const bool wf = cmu == Lmu - 1, wb = cmu == 0;
+    const int jf = wf ? site - (Lmu - 1) * stride : site + stride;
+    const int jb = wb ? site + (Lmu - 1) * stride : site - stride;
+    cx<R> uf[3][3], ub[3][3], pf[4][3], pb[4][3];
+    load_link<S, R, REC>(a.U, MU, Vp, (unsigned)site, uf);
+    load_spinor<S, R>(x, Vp, (unsigned)jf, pf);
+    load_link<S, R, REC>(a.U, MU, Vp, (unsigned)jb, ub);
+    load_spinor<S, R>(x, Vp, (unsigned)jb, pb);
+    cx<R> hf[2][3], hb[2][3];
+    project<MU, -1>(pf, hf);
+    project<MU, +1>(pb, hb);
+    if (MU == 0) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                hf[k][c] = phase_mul<S>(ph, hf[k][c], k, c, a.n == 1);
+                hb[k][c] = phase_mul<S>(cmk(ph.x, -ph.y), hb[k][c], k, c, a.n == 1);
+            }
+    }
+    if (__any(wf || wb)) {
+        const R bc = (R)a.g.bcf[MU];
+        const R sf = wf ? bc : (R)1, sb = wb ? bc : (R)1;
+        const bool zf = sf == (R)0, zb = sb == (R)0;
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                hf[k][c] = zf ? cmk((R)0, (R)0) : cscale(hf[k][c], sf);
+                hb[k][c] = zb ? cmk((R)0, (R)0) : cscale(hb[k][c], sb);
+            }
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int aa = 0; aa < 3; ++aa) {
+            cx<R> t = REC && aa == 2 ? cmul_i(uf[aa][0], hf[k][0]) : cmul(uf[aa][0], hf[k][0]);
+            cfma(t, uf[aa][1], hf[k][1]);
+            cfma(t, uf[aa][2], hf[k][2]);
+            out[(k * 3 + aa) * 64] = t;
+            cx<R> w = MU == 0 ? cmulc(ub[0][aa], hb[k][0]) : cmulc_r(ub[0][aa], hb[k][0]);
+            cfmac(w, ub[1][aa], hb[k][1]);
+            cfmac(w, ub[2][aa], hb[k][2]);
+            out[(6 + k * 3 + aa) * 64] = w;
+        }
+}
+
+// acc + component (SP, c) of (1 + SGN gamma_MU) expansion of g (stride 64).
+template <int MU, int SGN, int SP, class R>
+__device__ __forceinline__ cx<R> add_hop(cx<R> acc, const cx<R> *__restrict__ g, int c)
+{
+    constexpr int k = SP < 2 ? SP : (MU == 0 || MU == 1) ? 3 - SP : SP - 2;   // half-spinor row it takes
+    const cx<R> v = g[(k * 3 + c) * 64];
+    if constexpr (SP < 2) return cadd(acc, v);
+    else if constexpr (MU == 0) return cadd(acc, SGN < 0 ? cnimul(v) : cimul(v));
+    else if constexpr (MU == 1) return ((SGN < 0) == (SP == 2)) ? csub(acc, v) : cadd(acc, v);
+    else if constexpr (MU == 2) return cadd(acc, ((SGN < 0) == (SP == 2)) ? cnimul(v) : cimul(v));
+    else return SGN < 0 ? csub(acc, v) : cadd(acc, v);
+}
+
+// Sum of the eight hops for component K = 3 spin + colour, in hop order.
+template <int K, class R>
+__device__ __forceinline__ cx<R> sum_hops(const cx<R> *__restrict__ g)
+{
+    constexpr int SP = K / 3, H = 6 * 64;
+    const int c = K % 3;
+    cx<R> acc = cmk((R)0, (R)0);
+    acc = add_hop<0, -1, SP>(acc, g, c);
+    acc = add_hop<0, +1, SP>(acc, g + H, c);
+    acc = add_hop<1, -1, SP>(acc, g + 2 * H, c);
+    acc = add_hop<1, +1, SP>(acc, g + 3 * H, c);
+    acc = add_hop<2, -1, SP>(acc, g + 4 * H, c);
+    acc = add_hop<2, +1, SP>(acc, g + 5 * H, c);
+    acc = add_hop<3, -1, SP>(acc, g + 6 * H, c);
+    return add_hop<3, +1, SP>(acc, g + 7 * H, c);
+}
+
+template <class S, bool HW, bool EPI, bool REC, bool NT>
+__global__ __launch_bounds__(256, 2) void k_dslash_dir(DsArgs<S> a)
+{
+    using R = typename StoreT<S>::real;
+    using U = UnitOf<S>;
+    using T = typename U::T;
+    __shared__ cx<R> hop[8 * 6 * 64];
+    const Geo &g = a.g;
+    const int Vp = g.Vp;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = (int)(threadIdx.x & 63);
+    // grid: x = XCDs x right-hand sides, y = site blocks of an XCD (one "XCD" for small lattices)
+    const int xcd = a.xcd_remap ? (int)(blockIdx.x & 7) : 0;
+    const int j = a.xcd_remap ? (int)(blockIdx.x >> 3) : (int)blockIdx.x;
+    int site;
+    if (a.order == 1 || a.order == 3) site = slab_site(g, a.order, a.cols, xcd, (int)blockIdx.y * 64 + lane);
+    else site = (xcd * (int)gridDim.y + (int)blockIdx.y) * 64 + lane;
+    const int s = a.slots ? a.slots[j] : j;
+    const size_t off = (size_t)s * (size_t)a.fstride;
+    const S *x = a.x + off;
+
+    const bool real = site < g.V;
+    const int s0 = real ? site : 0;   // other lanes load site 0 and drop the result
+    int xc, yc, zc, tc;
+    site_coords(g, s0, xc, yc, zc, tc);
+    // units this wave writes, from q0 on: three of twelve, or of six one for waves 0 and 1 (wave 0
+    // has the background phase to apply) and two for waves 2 and 3
+    constexpr int NMINE = U::C == 2 ? 2 : 3;
+    const int q0 = U::C == 2 ? (wave < 2 ? wave : 2 * wave - 2) : 3 * wave;
+    const int nmine = U::C == 2 ? (wave < 2 ? 1 : 2) : 3;
+    T own[NMINE], ep[3][NMINE];
+    const S *e[3] = {a.e1, a.e2, a.e3};
+#pragma unroll
+    for (int i = 0; i < NMINE; ++i) {
+        const int q = i < nmine ? q0 + i : q0;
+        own[i] = ld_unit<S, false>(x, Vp, q, (unsigned)s0);
+        if constexpr (EPI) {
+#pragma unroll
+            for (int t = 0; t < 3; ++t)
+                if (e[t]) ep[t][i] = ld_unit<S, NT>(e[t] + off, Vp, q, (unsigned)s0);
+        }
+    }
+    cx<R> *out = hop + wave * 12 * 64 + lane;
+    if (wave == 0) {
+        const int grp = a.fgroup ? a.fgroup[s] : 0;
+        const cx<double> pd = a.phase[grp * g.Lt + tc];
+        dir_hops<0, S, REC>(a, x, s0, xc, g.Lx, 1, cmk((R)pd.x, (R)pd.y), out);
+    } else if (wave == 1) {
+        dir_hops<1, S, REC>(a, x, s0, yc, g.Ly, g.Lx, cmk((R)1, (R)0), out);
+    } else if (wave == 2) {
+        dir_hops<2, S, REC>(a, x, s0, zc, g.Lz, g.Lxy, cmk((R)1, (R)0), out);
+    } else {
+        dir_hops<3, S, REC>(a, x, s0, tc, g.Lt, g.Lxyz, cmk((R)1, (R)0), out);
+    }
+    __syncthreads();
+    if (site >= Vp) return;   // beyond the slab or the lattice
+
+    const R diag = (R)a.diag, sc = (R)a.a;
+    const R cc[3] = {(R)a.c1, (R)a.c2, (R)a.c3};
+    const cx<R> *hp = hop + lane;
+    auto finish = [&](auto qc, int i) {
+        constexpr int Q = decltype(qc)::value;
+        const R sg = (HW && Q >= U::N / 2) ? -sc : sc;
+        cx<R> acc[U::C];
+        acc[0] = sum_hops<Q * U::C>(hp);
+        if constexpr (U::C == 2) acc[1] = sum_hops<Q * U::C + 1>(hp);
+        T v;
+#pragma unroll
+        for (int h = 0; h < U::C; ++h) {
+            v.c[h] = cscale(site_term(diag, own[i].c[h], acc[h]), sg);
+            if constexpr (EPI) {
+#pragma unroll
+                for (int t = 0; t < 3; ++t)
+                    if (e[t]) v.c[h] = add_scaled(v.c[h], cc[t], ep[t][i].c[h]);
+            }
+            if (!real) v.c[h] = cmk((R)0, (R)0);   // padding sites hold zeros in every field
+        }
+        st_unit<S, NT>(a.y + off, Vp, Q, (unsigned)site, v);
+    };
+#define OV_UNIT(Q, I) finish(std::integral_constant<int, Q>{}, I)
+    if constexpr (U::C == 2) {
+        if (wave == 0) { OV_UNIT(0, 0); }
+        else if (wave == 1) { OV_UNIT(1, 0); }
+        else if (wave == 2) { OV_UNIT(2, 0); OV_UNIT(3, 1); }
+        else { OV_UNIT(4, 0); OV_UNIT(5, 1); }
+    } else {
+        if (wave == 0) { OV_UNIT(0, 0); OV_UNIT(1, 1); OV_UNIT(2, 2); }
+        else if (wave == 1) { OV_UNIT(3, 0); OV_UNIT(4, 1); OV_UNIT(5, 2); }
+        else if (wave == 2) { OV_UNIT(6, 0); OV_UNIT(7, 1); OV_UNIT(8, 2); }
+        else { OV_UNIT(9, 0); OV_UNIT(10, 1); OV_UNIT(11, 2); }
+    }
+#undef OV_UNIT
+}
+
+template <class S, bool REC, bool NT>
+static void launch_dir_kernel(const DsArgs<S> &b, bool hw, bool epi, dim3 grid, hipStream_t st)
+{
+    if (epi) hipLaunchKernelGGL((k_dslash_dir<S, true, true, REC, NT>), grid, dim3(256), 0, st, b);
+    else if (hw) hipLaunchKernelGGL((k_dslash_dir<S, true, false, REC, NT>), grid, dim3(256), 0, st, b);
+    else hipLaunchKernelGGL((k_dslash_dir<S, false, false, REC, NT>), grid, dim3(256), 0, st, b);
+}
+
+template <class S>
+hipError_t launch_dslash_dir(const DsArgs<S> &a, bool hw, bool epi, hipStream_t st)
+{
+    if (a.n <= 0) return hipSuccess;
+    DsArgs<S> b = a;
+    b.cols = 1;
+    if (b.order == 1 && (a.g.Lz % 8 != 0 || a.g.V % 64 != 0)) b.order = 0;
+    if (b.order == 3 && (a.g.Lt % 8 != 0 || a.g.V % 64 != 0)) b.order = 0;
+    const int nsb = a.g.Vp / 64;
+    // from 64 site blocks on, each XCD takes a contiguous run of them, and the right-hand sides of a
+    // site block follow each other on its XCD (they share the links in its L2)
+    b.xcd_remap = (b.order != 0 || nsb >= 64) ? 1 : 0;
+    const int ny = b.order != 0 ? (a.g.V / 8 + 63) / 64 : b.xcd_remap ? (nsb + 7) / 8 : nsb;
+    if (ny > 65535 || a.n > (1 << 24)) return hipErrorInvalidValue;
+    const dim3 grid(b.xcd_remap ? 8 * a.n : a.n, ny);
+    if (a.recon) {
+        if (a.stream_hint) launch_dir_kernel<S, true, true>(b, hw, epi, grid, st);
+        else launch_dir_kernel<S, true, false>(b, hw, epi, grid, st);
+    } else {
+        if (a.stream_hint) launch_dir_kernel<S, false, true>(b, hw, epi, grid, st);
+        else launch_dir_kernel<S, false, false>(b, hw, epi, grid, st);
+    }
+    return hipGetLastError();
+}
+
+template hipError_t launch_dslash_dir<double2>(const DsArgs<double2> &, bool, bool, hipStream_t);
+template hipError_t launch_dslash_dir<float2>(const DsArgs<float2> &, bool, bool, hipStream_t);
+template hipError_t launch_dslash_dir<uint32_t>(const DsArgs<uint32_t> &, bool, bool, hipStream_t);
+
+}  // namespace ov

@@ -15,161 +15,12 @@
 // so the neighbour spinor is reduced to a half spinor h0, h1 (2 x 3 complex),
 // multiplied by the 3x3 link and expanded back.  One thread owns one site and
 // NR right-hand sides: the link is loaded once and applied to all NR spinors.
-#include "ov_device.h"
+#pragma once
+
+#include "dslash_device.h"
 #include "ov_internal.h"
-#include "spin.h"
 
 namespace ov {
-
-// Loads address a plane through a wave-uniform base pointer plus a 32-bit
-// per-lane site offset, so that the compiler can use scalar-base addressing
-// instead of per-lane 64-bit address arithmetic.
-template <class S, class R>
-__device__ __forceinline__ cx<R> ldp(const S *__restrict__ plane, unsigned site)
-{
-    const unsigned boff = site * (unsigned)sizeof(S);   // < 4 GiB: a plane holds at most 2^31/64 sites
-    return ldc<R>((const S *)((const char *)plane + boff), 0u);
-}
-
-template <class S, class R>
-__device__ __forceinline__ void stp(S *__restrict__ plane, unsigned site, cx<R> v)
-{
-    const unsigned boff = site * (unsigned)sizeof(S);
-    stc<R>((S *)((char *)plane + boff), 0u, v);
-}
-
-// Components k = 2p and 2p+1 of one site: a single 16-byte load for the
-// paired FP32 layout, two plane loads otherwise.
-template <class S, class R>
-__device__ __forceinline__ void ldpair(const S *__restrict__ f, int Vp, int p, unsigned site, cx<R> &a, cx<R> &b)
-{
-    if constexpr (Pair<S>::E == 2) {
-        const float4 v = *(const float4 *)((const char *)(f + (size_t)(2 * p) * (unsigned)Vp) + site * 16u);
-        a = cmk((R)v.x, (R)v.y);
-        b = cmk((R)v.z, (R)v.w);
-    } else {
-        a = ldp<S, R>(f + (size_t)(2 * p) * (unsigned)Vp, site);
-        b = ldp<S, R>(f + (size_t)(2 * p + 1) * (unsigned)Vp, site);
-    }
-}
-
-template <class S, class R>
-__device__ __forceinline__ void stpair(S *__restrict__ f, int Vp, int p, unsigned site, cx<R> a, cx<R> b)
-{
-    if constexpr (Pair<S>::E == 2) {
-        *(float4 *)((char *)(f + (size_t)(2 * p) * (unsigned)Vp) + site * 16u) =
-            make_float4((float)a.x, (float)a.y, (float)b.x, (float)b.y);
-    } else {
-        stp<S, R>(f + (size_t)(2 * p) * (unsigned)Vp, site, a);
-        stp<S, R>(f + (size_t)(2 * p + 1) * (unsigned)Vp, site, b);
-    }
-}
-
-// Non-temporal variants for operands that are touched once per launch (the
-// epilogue inputs and the output): the loads and stores carry the
-// non-temporal hint so that they do not displace the stencil's neighbour
-// spinors and links from L2.
-typedef float ov_f4 __attribute__((ext_vector_type(4)));
-typedef double ov_d2 __attribute__((ext_vector_type(2)));
-
-template <class S, class R>
-__device__ __forceinline__ cx<R> ldp_nt(const S *__restrict__ plane, unsigned site)
-{
-    const char *p = (const char *)plane + site * (unsigned)sizeof(S);
-    if constexpr (sizeof(S) == 16) {
-        const ov_d2 v = __builtin_nontemporal_load((const ov_d2 *)p);
-        return cmk((R)v.x, (R)v.y);
-    } else if constexpr (sizeof(S) == 4) {
-        const uint32_t v = __builtin_nontemporal_load((const uint32_t *)p);
-        return cmk((R)bf16_lo(v), (R)bf16_hi(v));
-    } else {
-        return ldp<S, R>(plane, site);
-    }
-}
-
-template <class S, class R>
-__device__ __forceinline__ void stp_nt(S *__restrict__ plane, unsigned site, cx<R> v)
-{
-    char *p = (char *)plane + site * (unsigned)sizeof(S);
-    if constexpr (sizeof(S) == 16) {
-        ov_d2 w = {(double)v.x, (double)v.y};
-        __builtin_nontemporal_store(w, (ov_d2 *)p);
-    } else if constexpr (sizeof(S) == 4) {
-        const uint32_t w = f2bf((float)v.x) | (f2bf((float)v.y) << 16);
-        __builtin_nontemporal_store(w, (uint32_t *)p);
-    } else {
-        stp<S, R>(plane, site, v);
-    }
-}
-
-template <class S, class R>
-__device__ __forceinline__ void ldpair_nt(const S *__restrict__ f, int Vp, int p, unsigned site, cx<R> &a, cx<R> &b)
-{
-    if constexpr (Pair<S>::E == 2) {
-        const ov_f4 v = __builtin_nontemporal_load(
-            (const ov_f4 *)((const char *)(f + (size_t)(2 * p) * (unsigned)Vp) + site * 16u));
-        a = cmk((R)v.x, (R)v.y);
-        b = cmk((R)v.z, (R)v.w);
-    } else {
-        a = ldp_nt<S, R>(f + (size_t)(2 * p) * (unsigned)Vp, site);
-        b = ldp_nt<S, R>(f + (size_t)(2 * p + 1) * (unsigned)Vp, site);
-    }
-}
-
-template <class S, class R>
-__device__ __forceinline__ void stpair_nt(S *__restrict__ f, int Vp, int p, unsigned site, cx<R> a, cx<R> b)
-{
-    if constexpr (Pair<S>::E == 2) {
-        const ov_f4 w = {(float)a.x, (float)a.y, (float)b.x, (float)b.y};
-        __builtin_nontemporal_store(w, (ov_f4 *)((char *)(f + (size_t)(2 * p) * (unsigned)Vp) + site * 16u));
-    } else {
-        stp_nt<S, R>(f + (size_t)(2 * p) * (unsigned)Vp, site, a);
-        stp_nt<S, R>(f + (size_t)(2 * p + 1) * (unsigned)Vp, site, b);
-    }
-}
-
-// Link U_mu(s): components 0..7 as pairs, component 8 on its own plane.
-// REC: only the first two rows are read (components 0..5, three pairs) and
-// the third is rebuilt as u_2a = conj(u_0b u_1c - u_0c u_1b), (a, b, c)
-// cyclic, the identity that an SU(3) matrix (unitary, det 1) satisfies.  The
-// gauge upload measures how far the stored links are from it and selects
-// these kernels only where it holds to FP64 rounding; they read two thirds of
-// the link bytes.
-template <class R>
-__device__ __forceinline__ void rebuild_row2(cx<R> (&u)[3][3])
-{
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const int b1 = (a + 1) % 3, c1 = (a + 2) % 3;
-        const cx<R> t = csub(cmul(u[0][b1], u[1][c1]), cmul(u[0][c1], u[1][b1]));
-        u[2][a] = cmk(t.x, -t.y);
-    }
-}
-
-template <class S, class R, bool REC>
-__device__ __forceinline__ void load_link(const S *__restrict__ U, int mu, int Vp, unsigned s, cx<R> (&u)[3][3])
-{
-    const S *b = U + (size_t)(mu * 9) * (unsigned)Vp;
-    if constexpr (REC) {
-#pragma unroll
-        for (int p = 0; p < 3; ++p)
-            ldpair<S, R>(b, Vp, p, s, u[(2 * p) / 3][(2 * p) % 3], u[(2 * p + 1) / 3][(2 * p + 1) % 3]);
-        rebuild_row2(u);
-    } else {
-#pragma unroll
-        for (int p = 0; p < 4; ++p)
-            ldpair<S, R>(b, Vp, p, s, u[(2 * p) / 3][(2 * p) % 3], u[(2 * p + 1) / 3][(2 * p + 1) % 3]);
-        u[2][2] = ldp<S, R>(b + (size_t)8 * (unsigned)Vp, s);
-    }
-}
-
-template <class S, class R>
-__device__ __forceinline__ void load_spinor(const S *__restrict__ x, int Vp, unsigned s, cx<R> (&p)[4][3])
-{
-#pragma unroll
-    for (int q = 0; q < 6; ++q)
-        ldpair<S, R>(x, Vp, q, s, p[(2 * q) / 3][(2 * q) % 3], p[(2 * q + 1) / 3][(2 * q + 1) % 3]);
-}
 
 // Output of one site: v_k = a G (diag x_k - acc_k / 2) + c1 e1_k + c2 e2_k + c3 e3_k.
 template <class S, class R, bool HW, bool EPI>
@@ -187,8 +38,7 @@ __device__ __forceinline__ void write_site(const DsArgs<S> &a, size_t off, unsig
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int k = 2 * q + h, sp = k / 3, c = k % 3;
-            v[h] = cmk(diag * x[sp][c].x - (R)0.5 * acc[sp][c].x, diag * x[sp][c].y - (R)0.5 * acc[sp][c].y);
-            v[h] = cscale(v[h], (HW && sp >= 2) ? -sc : sc);
+            v[h] = cscale(site_term(diag, x[sp][c], acc[sp][c]), (HW && sp >= 2) ? -sc : sc);
         }
         if (EPI) {
 #pragma unroll
@@ -198,10 +48,7 @@ __device__ __forceinline__ void write_site(const DsArgs<S> &a, size_t off, unsig
                 if (nt) ldpair_nt<S, R>(ep[t] + off, Vp, q, site, e[0], e[1]);
                 else ldpair<S, R>(ep[t] + off, Vp, q, site, e[0], e[1]);
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    v[h].x = fma(cc[t], e[h].x, v[h].x);
-                    v[h].y = fma(cc[t], e[h].y, v[h].y);
-                }
+                for (int h = 0; h < 2; ++h) v[h] = add_scaled(v[h], cc[t], e[h]);
             }
         }
         if (nt) stpair_nt<S, R>(a.y + off, Vp, q, site, v[0], v[1]);
@@ -214,6 +61,7 @@ __device__ __forceinline__ void write_site(const DsArgs<S> &a, size_t off, unsig
 // is wanted (s or s - mu).
 template <class S, class R, bool REC>
 struct GlobalLinks {   // straight from the packed link field
+    static constexpr bool rebuilt = REC;   // the third row comes from the first two
     const S *U;
     int Vp;
     __device__ __forceinline__ void operator()(int mu, int, unsigned site, cx<R> (&u)[3][3]) const
@@ -224,9 +72,10 @@ struct GlobalLinks {   // straight from the packed link field
 
 // Staged in LDS by the workgroup: [slot][component][site slot], SL site
 // slots, E components per link (9, or 6 when the third row is rebuilt at
-// each read: RB).
-template <class R, int E, bool RB, int SL>
+// each read: RB; with nine of them the stage rebuilt it).
+template <class R, int E, bool REC, int SL>
 struct LdsLinks {
+    static constexpr bool rebuilt = REC, RB = REC && E == 6;
     const cx<R> *base;
     int sl;   // this thread's site slot
     __device__ __forceinline__ void operator()(int, int slot, unsigned, cx<R> (&u)[3][3]) const
@@ -275,13 +124,13 @@ __device__ __forceinline__ void hop_dir(const DsArgs<S> &a, const LF &links, int
 #pragma unroll
                     for (int k = 0; k < 2; ++k)
 #pragma unroll
-                        for (int c = 0; c < 3; ++c) h[k][c] = cmul(f, h[k][c]);
+                        for (int c = 0; c < 3; ++c) h[k][c] = phase_mul<S>(f, h[k][c], k, c, a.n == 1);
                 }
 #pragma unroll
                 for (int k = 0; k < 2; ++k)
 #pragma unroll
                     for (int aa = 0; aa < 3; ++aa) {
-                        cx<R> t = cmul(u[aa][0], h[k][0]);
+                        cx<R> t = LF::rebuilt && aa == 2 ? cmul_i(u[aa][0], h[k][0]) : cmul(u[aa][0], h[k][0]);
                         cfma(t, u[aa][1], h[k][1]);
                         cfma(t, u[aa][2], h[k][2]);
                         g[k][aa] = t;
@@ -309,13 +158,13 @@ __device__ __forceinline__ void hop_dir(const DsArgs<S> &a, const LF &links, int
 #pragma unroll
                     for (int k = 0; k < 2; ++k)
 #pragma unroll
-                        for (int c = 0; c < 3; ++c) h[k][c] = cmul(f, h[k][c]);
+                        for (int c = 0; c < 3; ++c) h[k][c] = phase_mul<S>(f, h[k][c], k, c, a.n == 1);
                 }
 #pragma unroll
                 for (int k = 0; k < 2; ++k)
 #pragma unroll
                     for (int aa = 0; aa < 3; ++aa) {
-                        cx<R> t = cmulc(u[0][aa], h[k][0]);
+                        cx<R> t = MU == 0 ? cmulc(u[0][aa], h[k][0]) : cmulc_r(u[0][aa], h[k][0]);
                         cfmac(t, u[1][aa], h[k][1]);
                         cfmac(t, u[2][aa], h[k][2]);
                         g[k][aa] = t;
@@ -349,34 +198,13 @@ __device__ __forceinline__ int xcd_block(int b, int nblk)
 // per site, against 2/(Lz/8) for order 1).  orders 1 and 3 need Lz % 8 == 0
 // (Lt % 8 == 0) and V % 64 == 0 (no padding); the launcher checks.
 //
-// site_in_block gives the site of position tb (0 <= tb < spb) in workgroup
-// blockIdx.x when every workgroup covers spb sites.
+// slab_site gives the site of position u in the slab of XCD xcd (orders 1 and
+// 3); site_in_block that of position tb (0 <= tb < spb) in workgroup blockIdx.x
+// when every workgroup covers spb sites.
 __device__ __forceinline__ int site_in_block(const Geo &g, int order, int xcd_remap, int cols, int tb, int spb)
 {
-    if (order == 3) {
-        const int xcd = blockIdx.x & 7;
-        const int u = (blockIdx.x >> 3) * spb + tb;
-        const int nt = g.Lt >> 3;
-        const int q = u / g.Lxy, o = u - q * g.Lxy;
-        if (q >= nt * g.Lz) return g.Vp;   // beyond the slab: no work
-        const int tl = q % nt, z = q / nt;
-        return o + g.Lxy * (z + g.Lz * (xcd * nt + tl));
-    }
-    if (order == 1) {
-        // with cols > 1 the slab is walked one y-column (Ly/cols rows) at a time,
-        // which shortens the distance between a site and its t neighbours
-        const int xcd = blockIdx.x & 7;
-        const int u = (blockIdx.x >> 3) * spb + tb;
-        const int nz = g.Lz >> 3;
-        const int P = g.Lxy / cols;                 // sites of one column in one (z, t) plane
-        const int per_col = P * nz * g.Lt;
-        const int col = u / per_col;
-        if (col >= cols) return g.Vp;               // beyond the slab: no work
-        const int rem = u - col * per_col;
-        const int q = rem / P, o = rem - q * P + col * P;
-        const int zl = q % nz, t = q / nz;
-        return o + g.Lxy * (xcd * nz + zl + g.Lz * t);
-    }
+    if (order == 1 || order == 3)
+        return slab_site(g, order, cols, blockIdx.x & 7, (blockIdx.x >> 3) * spb + tb);
     const int blk = xcd_remap ? xcd_block(blockIdx.x, gridDim.x) : blockIdx.x;
     return blk * spb + tb;
 }
@@ -535,15 +363,6 @@ __device__ __forceinline__ void stage_link(const DsArgs<S> &a, int slot, int s, 
     }
 }
 
-__device__ __forceinline__ void site_coords(const Geo &g, int s, int &xc, int &yc, int &zc, int &tc)
-{
-    int rem = s;
-    xc = rem % g.Lx; rem /= g.Lx;
-    yc = rem % g.Ly; rem /= g.Ly;
-    zc = rem % g.Lz;
-    tc = rem / g.Lz;
-}
-
 template <class S, int NR, int Q, bool HW, bool EPI, bool REC>
 __global__ __launch_bounds__(512) void k_dslash_lds(DsArgs<S> a)
 {
@@ -589,7 +408,7 @@ __global__ __launch_bounds__(512) void k_dslash_lds(DsArgs<S> a)
     if (site >= g.Vp) return;
     const int sub = lane / SL;
     const int j0 = ((blockIdx.y * W + wave) * Q + sub) * NR;
-    const LdsLinks<R, E, REC && E == 6, SL> lf{lk, sl};
+    const LdsLinks<R, E, REC, SL> lf{lk, sl};
     dslash_body_at<S, NR, Q, HW, EPI>(a, site, xc, yc, zc, tc, j0, lf);
 }
 
@@ -688,7 +507,7 @@ __global__ __launch_bounds__(64 * W) void k_dslash_tm(DsArgs<S> a)
                 for (int k = 0; k < 2; ++k)
 #pragma unroll
                     for (int aa = 0; aa < 3; ++aa) {
-                        cx<R> tt = cmul(utc[aa][0], h[k][0]);
+                        cx<R> tt = REC && aa == 2 ? cmul_i(utc[aa][0], h[k][0]) : cmul(utc[aa][0], h[k][0]);
                         cfma(tt, utc[aa][1], h[k][1]);
                         cfma(tt, utc[aa][2], h[k][2]);
                         gg[k][aa] = tt;
@@ -709,7 +528,7 @@ __global__ __launch_bounds__(64 * W) void k_dslash_tm(DsArgs<S> a)
                 for (int k = 0; k < 2; ++k)
 #pragma unroll
                     for (int aa = 0; aa < 3; ++aa) {
-                        cx<R> tt = cmulc(utm[0][aa], h[k][0]);
+                        cx<R> tt = cmulc_r(utm[0][aa], h[k][0]);
                         cfmac(tt, utm[1][aa], h[k][1]);
                         cfmac(tt, utm[2][aa], h[k][2]);
                         gg[k][aa] = tt;
@@ -920,9 +739,5 @@ hipError_t launch_dslash(const DsArgs<S> &a, bool hw, bool epi, int nr, int bloc
     default: return hipErrorInvalidValue;
     }
 }
-
-template hipError_t launch_dslash<double2>(const DsArgs<double2> &, bool, bool, int, int, int, hipStream_t);
-template hipError_t launch_dslash<float2>(const DsArgs<float2> &, bool, bool, int, int, int, hipStream_t);
-template hipError_t launch_dslash<uint32_t>(const DsArgs<uint32_t> &, bool, bool, int, int, int, hipStream_t);
 
 }  // namespace ov

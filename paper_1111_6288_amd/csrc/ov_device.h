@@ -28,16 +28,36 @@ template <class R>
 __device__ __forceinline__ cx<R> cadd(cx<R> a, cx<R> b) { return {a.x + b.x, a.y + b.y}; }
 template <class R>
 __device__ __forceinline__ cx<R> csub(cx<R> a, cx<R> b) { return {a.x - b.x, a.y - b.y}; }
+// Products name which of their two multiplications is fused into the sum, so
+// that every kernel rounds alike wherever the compiler finds them: the dslash
+// kernels give the same bits for every launch shape.
+// a * b
 template <class R>
 __device__ __forceinline__ cx<R> cmul(cx<R> a, cx<R> b)
 {
-    return {a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x};
+#pragma clang fp contract(off)
+    return {fma(a.x, b.x, -(a.y * b.y)), fma(a.y, b.x, a.x * b.y)};
+}
+// a * b, the other product of the imaginary part rounded first
+template <class R>
+__device__ __forceinline__ cx<R> cmul_i(cx<R> a, cx<R> b)
+{
+#pragma clang fp contract(off)
+    return {fma(a.x, b.x, -(a.y * b.y)), fma(a.x, b.y, a.y * b.x)};
 }
 // conj(a) * b
 template <class R>
 __device__ __forceinline__ cx<R> cmulc(cx<R> a, cx<R> b)
 {
-    return {a.x * b.x + a.y * b.y, a.x * b.y - a.y * b.x};
+#pragma clang fp contract(off)
+    return {fma(a.x, b.x, a.y * b.y), fma(a.x, b.y, -(a.y * b.x))};
+}
+// conj(a) * b, the other product of the real part rounded first
+template <class R>
+__device__ __forceinline__ cx<R> cmulc_r(cx<R> a, cx<R> b)
+{
+#pragma clang fp contract(off)
+    return {fma(a.y, b.y, a.x * b.x), fma(a.x, b.y, -(a.y * b.x))};
 }
 // acc += a * b
 template <class R>

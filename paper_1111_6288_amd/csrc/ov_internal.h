@@ -37,6 +37,9 @@ struct DsArgs {
 
 template <class S>
 hipError_t launch_dslash(const DsArgs<S> &a, bool hw, bool epi, int nr, int block, int split, hipStream_t st);
+// the direction-wave kernel (site orders 0, 1 and 3)
+template <class S>
+hipError_t launch_dslash_dir(const DsArgs<S> &a, bool hw, bool epi, hipStream_t st);
 
 // ---------------------------------------------------------------- lincomb
 template <class SI, class SO>

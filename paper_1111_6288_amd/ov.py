@@ -526,6 +526,9 @@ class Context:
                     or e.get("nrhs") != int(nrhs) or e.get("kind") not in self._KIND
                     or bool(e.get("two_row_links", two_row)) != two_row):
                 continue
+            if "ms_unchosen" in e and e["ms_unchosen"] <= e["ms_per_launch"]:
+                applied.append(e["kind"])   # no shape beat the library's own choice: leave it
+                continue
             defaults = {"stream_hint": 0, "rhs_split": 1, "cols": 1, "wshare": 1}
             self.set_launch_config(prec, e["kind"], **{k: e.get(k, defaults.get(k)) for k in self._CFG
                                                        if k in e or k in defaults})
