@@ -31,39 +31,81 @@ __device__ __forceinline__ double block_sum(double v)
 
 // ---------------------------------------------------------------- packing
 // canonical complex128 [n][V][4][3]  <->  internal field layout [slot]
+//
+// A workgroup moves 64 consecutive sites, 12 KiB of the canonical layout,
+// through LDS: its four waves read (write) them as twelve runs of 64
+// consecutive numbers and write (read) one plane run of 64 sites per wave and
+// step.  Straight from memory a lane strides 192 bytes, so that every one of
+// its twelve 16-byte accesses touches another line of each site.  Rows of 13
+// numbers in LDS (one of padding) put the 64 sites of a component into
+// different bank groups.
+constexpr int kPackRow = 13;
+
 template <class S>
-__global__ void k_pack_spinor(const double2 *__restrict__ in, S *__restrict__ out, long fstride,
-                              const int *slots, int n, int V, int Vp)
+__global__ __launch_bounds__(256) void k_pack_spinor(const double2 *__restrict__ in, S *__restrict__ out, long fstride,
+                                                     const int *slots, int n, int V, int Vp)
 {
-    const int site = blockIdx.x * blockDim.x + threadIdx.x;
-    const int j = blockIdx.y;
-    if (site >= Vp || j >= n) return;
-    const int s = slots ? slots[j] : j;
-    S *o = out + (long)s * fstride;
+    __shared__ double2 sh[64 * kPackRow];
+    const int j = blockIdx.y, q = (int)threadIdx.x;
+    const int base = blockIdx.x * 64;   // < Vp, a multiple of 64
+    const int nin = base < V ? (V - base < 64 ? V - base : 64) * 12 : 0;   // numbers of this block in the lattice
+    const double2 *src = in + ((long)j * V + base) * 12;
 #pragma unroll
-    for (int k = 0; k < 12; ++k) {
-        cx<double> v = {0.0, 0.0};
-        if (site < V) {
-            double2 w = in[((long)j * V + site) * 12 + k];
-            v = {w.x, w.y};
+    for (int r = 0; r < 3; ++r) {
+        const int i = q + 256 * r;
+        const double2 v = i < nin ? src[i] : make_double2(0.0, 0.0);
+        sh[(i / 12) * kPackRow + i % 12] = v;
+    }
+    __syncthreads();
+    S *o = out + (long)(slots ? slots[j] : j) * fstride;
+    const int lane = q & 63, wave = q >> 6;
+    const long site = base + lane;
+    if constexpr (Pair<S>::E == 2) {   // pair-planes: one 16-byte element per site
+#pragma unroll
+        for (int p = wave; p < 6; p += 4) {
+            const double2 a = sh[lane * kPackRow + 2 * p], b = sh[lane * kPackRow + 2 * p + 1];
+            *(float4 *)(o + cpos<S>(2 * p, site, Vp)) = make_float4((float)a.x, (float)a.y, (float)b.x, (float)b.y);
         }
-        stc<double>(o, cpos<S>(k, site, Vp), v);
+    } else {
+#pragma unroll
+        for (int k = wave; k < 12; k += 4) {
+            const double2 a = sh[lane * kPackRow + k];
+            stc<double>(o, cpos<S>(k, site, Vp), cx<double>{a.x, a.y});
+        }
     }
 }
 
 template <class S>
-__global__ void k_unpack_spinor(const S *__restrict__ in, double2 *__restrict__ out, long fstride,
-                                const int *slots, int n, int V, int Vp)
+__global__ __launch_bounds__(256) void k_unpack_spinor(const S *__restrict__ in, double2 *__restrict__ out, long fstride,
+                                                       const int *slots, int n, int V, int Vp)
 {
-    const int site = blockIdx.x * blockDim.x + threadIdx.x;
-    const int j = blockIdx.y;
-    if (site >= V || j >= n) return;
-    const int s = slots ? slots[j] : j;
-    const S *p = in + (long)s * fstride;
+    __shared__ double2 sh[64 * kPackRow];
+    const int j = blockIdx.y, q = (int)threadIdx.x;
+    const int base = blockIdx.x * 64;   // < V
+    const S *p = in + (long)(slots ? slots[j] : j) * fstride;
+    const int lane = q & 63, wave = q >> 6;
+    const long site = base + lane;      // < Vp
+    if constexpr (Pair<S>::E == 2) {
 #pragma unroll
-    for (int k = 0; k < 12; ++k) {
-        cx<double> v = ldc<double>(p, cpos<S>(k, site, Vp));
-        out[((long)j * V + site) * 12 + k] = make_double2(v.x, v.y);
+        for (int c = wave; c < 6; c += 4) {
+            const float4 v = *(const float4 *)(p + cpos<S>(2 * c, site, Vp));
+            sh[lane * kPackRow + 2 * c] = make_double2((double)v.x, (double)v.y);
+            sh[lane * kPackRow + 2 * c + 1] = make_double2((double)v.z, (double)v.w);
+        }
+    } else {
+#pragma unroll
+        for (int k = wave; k < 12; k += 4) {
+            const cx<double> v = ldc<double>(p, cpos<S>(k, site, Vp));
+            sh[lane * kPackRow + k] = make_double2(v.x, v.y);
+        }
+    }
+    __syncthreads();
+    const int nout = (V - base < 64 ? V - base : 64) * 12;
+    double2 *dst = out + ((long)j * V + base) * 12;
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+        const int i = q + 256 * r;
+        if (i < nout) dst[i] = sh[(i / 12) * kPackRow + i % 12];
     }
 }
 
@@ -414,7 +456,7 @@ hipError_t launch_pack_spinor(const double2 *in, S *out, long fstride, const int
                               int Vp, hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
-    dim3 grid((Vp + 255) / 256, n);
+    dim3 grid(Vp / 64, n);
     hipLaunchKernelGGL((k_pack_spinor<S>), grid, dim3(256), 0, st, in, out, fstride, slots, n, V, Vp);
     return hipGetLastError();
 }
@@ -424,7 +466,7 @@ hipError_t launch_unpack_spinor(const S *in, double2 *out, long fstride, const i
                                 int Vp, hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
-    dim3 grid((V + 255) / 256, n);
+    dim3 grid((V + 63) / 64, n);
     hipLaunchKernelGGL((k_unpack_spinor<S>), grid, dim3(256), 0, st, in, out, fstride, slots, n, V, Vp);
     return hipGetLastError();
 }
