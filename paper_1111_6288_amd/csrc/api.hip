@@ -120,7 +120,8 @@ struct ov_ctx {
     // dslash launch shape per precision and kind (0: plain, 1: fused Clenshaw epilogue)
     struct Launch {
         int nr = 2, block = 128, order = 0, cap = 0, stream_hint = 0, split = 1, cols = 1, wshare = 1;
-        bool chosen = false;   // set by the caller or the autotuner; otherwise dslash_launch picks per batch
+        bool chosen = false;   // set by the caller or the autotuner; otherwise launch_rule decides per batch
+        bool dir = false;      // direction waves (launch_rule only)
     };
     Launch tune[3][2];
 
@@ -435,25 +436,51 @@ template <>
 const uint32_t *links_of<uint32_t>(const ov_ctx *c) { return c->U16; }
 
 // ---------------------------------------------------------------- launch helpers
-// Kernel of a dslash launch whose shape nobody chose (ov_set_tuning and its
-// relatives, ov_autotune).  Small batches wait for memory latency, not
-// bandwidth, and take the direction-wave kernel: mean of the plain and the
-// fused launch inside a captured graph, FP64 12 RHS of 4^4 16.7 -> 5.2 us,
-// FP32 4 RHS of 8^3x16 16.3 -> 6.7 us (an empty graph node takes 1.6 us).
-// Its four waves hold their own copy of no link, but every right-hand side
-// reads (and rebuilds the third row of) all eight: one vector gains up to the
-// largest lattice (24^3x48 FP64 222 -> 175 us, FP32 96 -> 81), a batch until
-// its fields outgrow the caches and the link sharing of the site-parallel
-// kernels wins (12 RHS: FP64 12^3x24, 96 MB a field batch, 96 us against 100;
-// 16^3x32, 302 MB, 336 against 301).  BF16 halves the bytes but not the
-// arithmetic: 12 RHS of 8^3x16 (4.7 MB) 11.8 against 12.4 us, 4 RHS of
-// 12^3x24 (8 MB) 17.2 against 16.3.
+// Kernel and shape of a dslash launch that nobody chose (ov_set_tuning and its relatives,
+// ov_autotune), by the bytes of one field batch F = 12 V n and the batch size n.  All kernels and
+// shapes give the same bits.  Times are the mean of a plain and a fused launch in a captured graph
+// (an empty node takes 1.6 us).
+//
+// Direction waves for small batches, which wait for memory latency, not bandwidth: FP64 12 RHS of
+// 4^4 16.7 (two RHS per thread) -> 5.1 us, FP32 4 RHS of 8^3x16 16.3 -> 6.7 us.  Every right-hand
+// side reads all eight links and rebuilds their third rows, so a batch gains until its fields
+// outgrow the caches and sharing staged links wins (12 RHS FP64: 12^3x24, F = 96 MB, 96 us against
+// 100; 16^3x32, 302 MB, 336 against 301).  Up to three vectors gain on the largest lattice too
+// (one of 24^3x48: FP64 222 -> 157 us, FP32 96 -> 70).  BF16 halves the bytes but not the
+// arithmetic: 12 RHS of 8^3x16, 4.7 MB, 11.8 against 12.4 us, 4 RHS of 12^3x24, 8 MB, 17.2
+// against 16.3.
+//
+// Link sharing otherwise: the W waves of a workgroup hold W right-hand sides of the same sites.
+// W = 8, or the even split when more than half of a workgroup would idle (24^3x48 FP32: 12 RHS W 8
+// 736 us, W 6 742, W 4 742, two RHS per thread 1121; 9 RHS W 8 623, W 5 560; BF16 12 RHS W 8 509,
+// W 6 522, two per thread 554).  FP64 stages twice the bytes: W up to 4, split evenly (12 RHS W 4
+// 1531, W 8 1553, two per thread 2459; 5 RHS W 3 681, W 4 734).  BF16 with one or two vectors
+// keeps one thread for all of them (24^3x48, one vector: 48 us, direction waves 56).
+//
+// Site order: from F = 64 MB on z-slabs per XCD (t-slabs where Lz % 8), non-temporal own-site
+// streams (24^3x48 FP64 one vector: canonical order 175, z-slabs 164, with the hint 157); between
+// 16 and 64 MB t-slabs, which the caches still hold (16^3x32 FP64: 31.2 -> 28.4, z-slabs 29.9,
+// with the hint 31.0); below, canonical order.
 template <class S>
-bool dir_waves_rule(const Geo &g, int n)
+ov_ctx::Launch launch_rule(const Geo &g, int n)
 {
-    const double batch = 12.0 * sizeof(S) * g.V * n;
-    if (sizeof(S) == 4) return batch <= 7e6;
-    return n <= 3 || batch <= 96e6;
+    ov_ctx::Launch t;
+    const double F = 12.0 * sizeof(S) * g.V * n;
+    const bool zslab = g.Lz % 8 == 0 && g.V % 64 == 0, tslab = g.Lt % 8 == 0 && g.V % 64 == 0;
+    const bool bf16 = sizeof(S) == 4;
+    t.nr = 1;
+    t.dir = (bf16 ? F <= 7e6 : n <= 3 || F <= 96e6) && dslash_dir_fits(g);
+    t.stream_hint = F > 64e6 ? 1 : 0;
+    if (t.dir) {
+        t.order = F > 64e6 && zslab ? 1 : F > 16e6 && F <= 64e6 && tslab ? 3 : 0;
+    } else {
+        t.order = zslab ? 1 : tslab ? 3 : 0;
+        const int most = sizeof(S) == 16 ? 4 : 8, groups = (n + most - 1) / most;
+        const bool full = sizeof(S) != 16 && 2 * (most * groups - n) <= most;
+        if (bf16 && n <= 2) t.nr = 2;
+        else t.wshare = full ? most : (n + groups - 1) / groups;
+    }
+    return t;
 }
 
 template <class S>
@@ -482,7 +509,7 @@ int dslash_launch(ov_ctx *c, const Batch &b, const int *fgroup, const S *x, S *y
     d.c3 = c3;
     const int P = PrecOf<S>::p;
     const bool epi = e1 || e2 || e3;
-    const auto &tu = c->tune[P][epi ? 1 : 0];
+    const auto tu = c->tune[P][epi ? 1 : 0].chosen ? c->tune[P][epi ? 1 : 0] : launch_rule<S>(c->g, b.n);
     d.order = tu.order;
     d.blocks_per_cu = tu.cap;
     d.stream_hint = tu.stream_hint;
@@ -500,9 +527,7 @@ int dslash_launch(ov_ctx *c, const Batch &b, const int *fgroup, const S *x, S *y
     // input and epilogue field once, the output once
     const double bytes =
         (double)c->g.V * ((c->recon ? 24.0 : 36.0) * sb + (double)b.n * 12.0 * sb * (2 + nex));
-    if (!tu.chosen && dir_waves_rule<S>(c->g, b.n)) {
-        d.order = 0;
-        d.stream_hint = 0;
+    if (tu.dir) {
         int pi = prof_begin(c);
         HIPCHK(launch_dslash_dir<S>(d, hw || epi, epi, c->stream));
         prof_end(c, pi, epi ? PC_CLENSHAW : PC_DSLASH, bytes);
@@ -511,7 +536,7 @@ int dslash_launch(ov_ctx *c, const Batch &b, const int *fgroup, const S *x, S *y
     int nr = tu.nr, split = tu.split, ws = tu.wshare;
     while (split > 1 && (split / 2) * nr >= b.n) split /= 2;
     while (nr > 1 && nr / 2 >= b.n) nr /= 2;
-    while (ws > 1 && (ws / 2) * split * nr >= b.n) ws /= 2;   // no wave without a RHS
+    while (ws > 1 && (ws / 2) * split * nr >= b.n && tu.chosen) ws /= 2;   // no wave without a RHS
     d.wshare = ws;
     int pi = prof_begin(c);
     HIPCHK(launch_dslash<S>(d, hw || epi, epi, nr, tu.block, split, c->stream));

@@ -271,7 +271,7 @@ hipError_t launch_dslash_dir(const DsArgs<S> &a, bool hw, bool epi, hipStream_t 
     // site block follow each other on its XCD (they share the links in its L2)
     b.xcd_remap = (b.order != 0 || nsb >= 64) ? 1 : 0;
     const int ny = b.order != 0 ? (a.g.V / 8 + 63) / 64 : b.xcd_remap ? (nsb + 7) / 8 : nsb;
-    if (ny > 65535 || a.n > (1 << 24)) return hipErrorInvalidValue;
+    if (!dslash_dir_fits(a.g) || a.n > (1 << 24)) return hipErrorInvalidValue;
     const dim3 grid(b.xcd_remap ? 8 * a.n : a.n, ny);
     if (a.recon) {
         if (a.stream_hint) launch_dir_kernel<S, true, true>(b, hw, epi, grid, st);

@@ -316,8 +316,8 @@ __global__ __launch_bounds__(256) void k_dslash(DsArgs<S> a)
 }
 
 // ---------------------------------------------------------------------------
-// Link-sharing variant.  The W waves of a workgroup (W = blockDim / 64: 2, 4
-// or 8) cover the same 64/Q sites, each for its own Q NR right-hand sides, so
+// Link-sharing variant.  The W waves of a workgroup (W = blockDim / 64: 2 to
+// 8) cover the same 64/Q sites, each for its own Q NR right-hand sides, so
 // a workgroup covers 64/Q sites for W Q NR RHS.  Before the stencil the
 // workgroup copies the eight links its sites use (U_mu(s) and U_mu(s - mu))
 // into LDS; every wave then reads them there, so a link crosses HBM once per
@@ -703,7 +703,7 @@ hipError_t launch_dslash(const DsArgs<S> &a, bool hw, bool epi, int nr, int bloc
     if (a.n <= 0) return hipSuccess;
     if (block < 64 || block > 512 || (block & 63)) return hipErrorInvalidValue;
     if (a.order == 2 && a.g.V % 64 == 0) return launch_tm<S>(a, hw, epi, block, st);
-    if (a.wshare == 2 || a.wshare == 4 || a.wshare == 8) {   // waves share sites and staged links
+    if (a.wshare >= 2 && a.wshare <= 8) {   // waves share sites and staged links
         if (nr == 1) {
             if (split == 1) return launch_lds<S, 1, 1>(a, hw, epi, st);
             if (split == 2) return launch_lds<S, 1, 2>(a, hw, epi, st);

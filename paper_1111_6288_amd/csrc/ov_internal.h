@@ -32,12 +32,13 @@ struct DsArgs {
     int stream_hint;         // 1: epilogue inputs and the output bypass cache retention (non-temporal)
     int cols;                // order 1: the slab is walked as `cols` y-columns, one after the other
     int recon;               // 1: links are SU(3); read two rows and rebuild the third
-    int wshare;              // 1, or W = 2, 4, 8 waves per workgroup sharing sites and LDS-staged links
+    int wshare;              // 1, or W = 2..8 waves per workgroup sharing sites and LDS-staged links
 };
 
 template <class S>
 hipError_t launch_dslash(const DsArgs<S> &a, bool hw, bool epi, int nr, int block, int split, hipStream_t st);
-// the direction-wave kernel (site orders 0, 1 and 3)
+// the direction-wave kernel (site orders 0, 1 and 3); its grid holds the site blocks of an XCD in y
+inline bool dslash_dir_fits(const Geo &g) { return (g.Vp / 64 + 7) / 8 <= 65535; }
 template <class S>
 hipError_t launch_dslash_dir(const DsArgs<S> &a, bool hw, bool epi, hipStream_t st);
 

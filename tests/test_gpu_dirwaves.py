@@ -80,3 +80,26 @@ def test_dirichlet_neighbours_are_not_read_into_the_result():
     want = {0, 1, lx, lx * (ly - 1), lx * ly, lx * ly * (lz - 1), lx * ly * lz}   # itself, +x, +-y, +-z, +t
     assert bad == want
     ctx.close()
+
+
+@pytest.mark.parametrize("L,bc", [((16, 16, 16, 32), (2, 0, 0, 2)), ((15, 14, 13, 34), (0, 1, 2, 0))])
+def test_unchosen_launches_give_the_bits_of_a_chosen_shape(L, bc):
+    """Batches around every boundary of the launch rule, against two right-hand sides per thread: the same bits."""
+    U = synth.su3_links(L, 0.3, 5)
+    ctx = _ctx(L, bc, U, (2 / 3, -1 / 3), (1e-3, -1e-3))
+    V = synth.volume(L)
+    gen = torch.Generator(device="cuda").manual_seed(2)
+    x = torch.randn((13, V, 4, 3), dtype=torch.complex128, device="cuda", generator=gen)
+    cases = [(p, n, True) for p, ns in (("fp64", (1, 3, 4, 5, 9)), ("fp32", (1, 4, 7, 8, 9, 13)),
+                                        ("bf16", (1, 2, 3, 5, 9, 13))) for n in ns] + [("fp64", 5, False), ("fp32", 9, False)]
+    got = {}
+    for prec, n, rec in cases:
+        ctx.set_link_reconstruct(rec)
+        got[prec, n, rec] = ctx.dslash(x[:n].contiguous(), [j % 2 for j in range(n)], prec=prec)
+    for prec in ("fp64", "fp32", "bf16"):
+        ctx.set_launch_config(prec, "dslash", rhs_per_thread=2, block=128)
+    for prec, n, rec in cases:
+        ctx.set_link_reconstruct(rec)
+        ref = ctx.dslash(x[:n].contiguous(), [j % 2 for j in range(n)], prec=prec)
+        assert torch.equal(got[prec, n, rec], ref), (prec, n, rec)
+    ctx.close()
