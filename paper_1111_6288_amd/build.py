@@ -20,7 +20,7 @@ OBJDIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libov.so")
 ARCH = os.environ.get("OV_OFFLOAD_ARCH", "gfx950")
 
-SOURCES = ["dslash_fp64.hip", "dslash_fp32.hip", "dslash_bf16.hip", "dslash_dir.hip", "blas.hip", "proj.hip", "force.hip",
+SOURCES = ["dslash_fp64.hip", "dslash_fp32.hip", "dslash_bf16.hip", "dslash_dir.hip", "dslash_share.hip", "blas.hip", "proj.hip", "force.hip",
            "api.hip", "dense.cpp"]
 
 FLAGS = [

@@ -452,9 +452,9 @@ const uint32_t *links_of<uint32_t>(const ov_ctx *c) { return c->U16; }
 //
 // Link sharing otherwise: the W waves of a workgroup hold W right-hand sides of the same sites.
 // W = 8, or the even split when more than half of a workgroup would idle (24^3x48 FP32: 12 RHS W 8
-// 736 us, W 6 742, W 4 742, two RHS per thread 1121; 9 RHS W 8 623, W 5 560; BF16 12 RHS W 8 509,
-// W 6 522, two per thread 554).  FP64 stages twice the bytes: W up to 4, split evenly (12 RHS W 4
-// 1531, W 8 1553, two per thread 2459; 5 RHS W 3 681, W 4 734).  BF16 with one or two vectors
+// 719 us, W 6 739, W 4 754, two RHS per thread 1121; 9 RHS W 8 623, W 5 560; BF16 12 RHS W 8 470,
+// W 4 490, two per thread 554).  FP64 stages twice the bytes: W up to 4, split evenly (12 RHS W 4
+// 1511, W 8 1607, two per thread 2459; 5 RHS W 3 681, W 4 734).  BF16 with one or two vectors
 // keeps one thread for all of them (24^3x48, one vector: 48 us, direction waves 56).
 //
 // Site order: from F = 64 MB on z-slabs per XCD (t-slabs where Lz % 8), non-temporal own-site

@@ -82,7 +82,7 @@ __device__ __forceinline__ void stp_nt(S *__restrict__ plane, unsigned site, cx<
         ov_d2 w = {(double)v.x, (double)v.y};
         __builtin_nontemporal_store(w, (ov_d2 *)p);
     } else if constexpr (sizeof(S) == 4) {
-        const uint32_t w = f2bf((float)v.x) | (f2bf((float)v.y) << 16);
+        const uint32_t w = pack_bf16((float)v.x, (float)v.y);
         __builtin_nontemporal_store(w, (uint32_t *)p);
     } else {
         stp<S, R>(plane, site, v);

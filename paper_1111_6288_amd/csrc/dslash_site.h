@@ -665,6 +665,23 @@ static hipError_t launch_lds_kernel(const DsArgs<S> &b, bool hw, bool epi, dim3 
     return hipGetLastError();
 }
 
+// Site order that the lattice allows, and the number of workgroups of spb sites that cover it.
+template <class S>
+inline int site_blocks(DsArgs<S> &b, int spb)
+{
+    const Geo &g = b.g;
+    b.xcd_remap = 0;
+    if (b.order == 1 && (g.Lz % 8 != 0 || g.V % 64 != 0)) b.order = 0;
+    if (b.cols < 1 || g.Ly % b.cols != 0) b.cols = 1;
+    if (b.order == 3 && (g.Lt % 8 != 0 || g.V % 64 != 0)) b.order = 0;
+    if (b.order == 2) b.order = 0;
+    if (b.order == 1 || b.order == 3) return 8 * ((g.V / 8 + spb - 1) / spb);
+    const int nbx = (g.Vp + spb - 1) / spb;   // the padding [V, Vp) is rewritten with zeros
+    if (nbx < 64) return nbx;
+    b.xcd_remap = 1;   // each XCD takes a contiguous run
+    return (nbx + 7) & ~7;
+}
+
 // Link-sharing launch: W = a.wshare waves per workgroup on the same 64/Q
 // sites; LDS holds the staged links (more if the occupancy cap asks for it).
 template <class S, int NR, int Q>
@@ -677,19 +694,8 @@ static hipError_t launch_lds(const DsArgs<S> &a, bool hw, bool epi, hipStream_t 
     const size_t need = (size_t)8 * E * SL * sizeof(cx<R>);
     const size_t capr = a.blocks_per_cu > 0 ? (size_t)(160 * 1024) / (size_t)a.blocks_per_cu - 256 : 0;
     const size_t lds = need > capr ? need : capr;
-    int nbx = (a.g.Vp + SL - 1) / SL;
     DsArgs<S> b = a;
-    b.xcd_remap = 0;
-    if (b.order == 1 && (a.g.Lz % 8 != 0 || a.g.V % 64 != 0)) b.order = 0;
-    if (b.cols < 1 || a.g.Ly % b.cols != 0) b.cols = 1;
-    if (b.order == 3 && (a.g.Lt % 8 != 0 || a.g.V % 64 != 0)) b.order = 0;
-    if (b.order == 2) b.order = 0;
-    if (b.order == 1 || b.order == 3) {
-        nbx = 8 * ((a.g.V / 8 + SL - 1) / SL);
-    } else if (nbx >= 64) {
-        nbx = (nbx + 7) & ~7;
-        b.xcd_remap = 1;
-    }
+    const int nbx = site_blocks(b, SL);
     const dim3 grid(nbx, (a.n + NR * Q * W - 1) / (NR * Q * W));
     if (a.recon) return launch_lds_kernel<S, NR, Q, true>(b, hw, epi, grid, W, lds, st);
     return launch_lds_kernel<S, NR, Q, false>(b, hw, epi, grid, W, lds, st);
@@ -705,7 +711,7 @@ hipError_t launch_dslash(const DsArgs<S> &a, bool hw, bool epi, int nr, int bloc
     if (a.order == 2 && a.g.V % 64 == 0) return launch_tm<S>(a, hw, epi, block, st);
     if (a.wshare >= 2 && a.wshare <= 8) {   // waves share sites and staged links
         if (nr == 1) {
-            if (split == 1) return launch_lds<S, 1, 1>(a, hw, epi, st);
+            if (split == 1) return launch_dslash_share<S>(a, hw, epi, st);
             if (split == 2) return launch_lds<S, 1, 2>(a, hw, epi, st);
             if (split == 4) return launch_lds<S, 1, 4>(a, hw, epi, st);
         } else if (nr == 2) {

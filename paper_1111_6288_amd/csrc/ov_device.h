@@ -102,6 +102,16 @@ __device__ __forceinline__ uint32_t f2bf(float f)
     return u >> 16;
 }
 
+// (re, im) as a BF16 pair: v_cvt_pk_bf16_f32, which rounds like f2bf for
+// every float (NaN stays NaN)
+__device__ __forceinline__ uint32_t pack_bf16(float x, float y)
+{
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+    const f2 v = {x, y};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, b2));
+}
+
 template <class S>
 struct StoreT;
 template <>
@@ -170,7 +180,7 @@ __device__ __forceinline__ void stc(float2 *p, unsigned i, cx<R> v)
 template <class R>
 __device__ __forceinline__ void stc(uint32_t *p, unsigned i, cx<R> v)
 {
-    p[i] = f2bf((float)v.x) | (f2bf((float)v.y) << 16);
+    p[i] = pack_bf16((float)v.x, (float)v.y);
 }
 
 template <class R>
@@ -186,7 +196,7 @@ __device__ __forceinline__ void stc(float2 *p, long i, cx<R> v)
 template <class R>
 __device__ __forceinline__ void stc(uint32_t *p, long i, cx<R> v)
 {
-    p[i] = f2bf((float)v.x) | (f2bf((float)v.y) << 16);
+    p[i] = pack_bf16((float)v.x, (float)v.y);
 }
 
 // ---------------------------------------------------------------- layouts

@@ -37,6 +37,9 @@ struct DsArgs {
 
 template <class S>
 hipError_t launch_dslash(const DsArgs<S> &a, bool hw, bool epi, int nr, int block, int split, hipStream_t st);
+// the link-sharing kernel: 2 <= a.wshare <= 8 waves, one right-hand side each (site orders 0, 1 and 3)
+template <class S>
+hipError_t launch_dslash_share(const DsArgs<S> &a, bool hw, bool epi, hipStream_t st);
 // the direction-wave kernel (site orders 0, 1 and 3); its grid holds the site blocks of an XCD in y
 inline bool dslash_dir_fits(const Geo &g) { return (g.Vp / 64 + 7) / 8 <= 65535; }
 template <class S>
