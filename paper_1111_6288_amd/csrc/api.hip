@@ -1133,6 +1133,7 @@ int ov_create(const int32_t L[4], const int32_t bc[4], double m_w, int device, o
     g.Vp = (int)((V + 63) / 64 * 64);
     g.Lxy = L[0] * L[1];
     g.Lxyz = L[0] * L[1] * L[2];
+    set_divisors(g);
     for (int m = 0; m < 4; ++m) g.bcf[m] = bc[m] == 0 ? 1.0f : (bc[m] == 1 ? -1.0f : 0.0f);
     c->stream = nullptr;   // the null stream until ov_set_stream names another one
     if (dev_alloc(c, (void **)&c->d_count, 256) != OV_OK) {

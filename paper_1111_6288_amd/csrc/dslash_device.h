@@ -184,13 +184,17 @@ __device__ __forceinline__ cx<R> add_scaled(cx<R> v, R c, cx<R> e)
     return {fma(c, e.x, v.x), fma(c, e.y, v.y)};
 }
 
+// Coordinates of a site (products instead of divisions, about twenty
+// instructions each).
 __device__ __forceinline__ void site_coords(const Geo &g, int s, int &xc, int &yc, int &zc, int &tc)
 {
-    int rem = s;
-    xc = rem % g.Lx; rem /= g.Lx;
-    yc = rem % g.Ly; rem /= g.Ly;
-    zc = rem % g.Lz;
-    tc = rem / g.Lz;
+    const unsigned a = __umulhi((unsigned)s, g.mul[0]) >> g.shr[0];
+    const unsigned b = __umulhi(a, g.mul[1]) >> g.shr[1];
+    const unsigned c = __umulhi(b, g.mul[2]) >> g.shr[2];
+    xc = s - (int)a * g.Lx;
+    yc = (int)a - (int)b * g.Ly;
+    zc = (int)b - (int)c * g.Lz;
+    tc = (int)c;
 }
 
 // Site of position u in the slab of XCD xcd (orders 1 and 3).
@@ -214,6 +218,92 @@ __device__ __forceinline__ int slab_site(const Geo &g, int order, int cols, int 
     const int q = rem / P, o = rem - q * P + col * P;
     const int zl = q % nz, t = q / nz;
     return o + g.Lxy * (xcd * nz + zl + g.Lz * t);
+}
+
+// One spinor as loaded, by buffer instructions: the plane is a scalar
+// resource and the site a 32-bit lane offset, so a load costs no vector
+// address arithmetic (with 64-bit lane addresses every load takes a 64-bit
+// add).  A resource covers exactly one plane.
+template <class S>
+struct RawSpinor {
+    using R = typename StoreT<S>::real;
+    static constexpr int C = Pair<S>::E, N = 12 / C, B = C * (int)sizeof(S);   // bytes of an element
+    uint32_t w[N][B / 4];
+
+    static __device__ __forceinline__ __amdgpu_buffer_rsrc_t plane(const S *f, int Vp, int q)
+    {
+        return __builtin_amdgcn_make_buffer_rsrc((void *)(f + (size_t)(q * C) * (unsigned)Vp), 0, (unsigned)Vp * B,
+                                                 0x00020000);
+    }
+    template <int AUX>
+    static __device__ __forceinline__ void ld(const S *f, int Vp, int q, unsigned boff, uint32_t (&o)[B / 4])
+    {
+        if constexpr (B == 16) {
+            const auto v = __builtin_amdgcn_raw_buffer_load_b128(plane(f, Vp, q), boff, 0, AUX);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o[i] = v[i];
+        } else {
+            o[0] = __builtin_amdgcn_raw_buffer_load_b32(plane(f, Vp, q), boff, 0, AUX);
+        }
+    }
+    // component h of an element
+    static __device__ __forceinline__ cx<R> get(const uint32_t (&o)[B / 4], int h)
+    {
+        if constexpr (sizeof(S) == 16) {
+            return cmk(__builtin_bit_cast(double, (uint64_t)o[0] | ((uint64_t)o[1] << 32)),
+                       __builtin_bit_cast(double, (uint64_t)o[2] | ((uint64_t)o[3] << 32)));
+        } else if constexpr (sizeof(S) == 8) {
+            return cmk(__uint_as_float(o[2 * h]), __uint_as_float(o[2 * h + 1]));
+        } else {
+            return cmk(bf16_lo(o[0]), bf16_hi(o[0]));
+        }
+    }
+    __device__ __forceinline__ void load(const S *f, int Vp, unsigned boff)
+    {
+#pragma unroll
+        for (int q = 0; q < N; ++q) ld<0>(f, Vp, q, boff, w[q]);
+    }
+    __device__ __forceinline__ void spinor(cx<R> (&p)[4][3]) const
+    {
+#pragma unroll
+        for (int k = 0; k < 12; ++k) p[k / 3][k % 3] = get(w[k / C], k % C);
+    }
+};
+
+// Byte offset inside a plane of the neighbour of site s0 (wrap: the hop
+// leaves the lattice; step +-stride, L the extent); across a Dirichlet
+// boundary one beyond every plane, which a buffer load answers with zeros.
+template <class S>
+__device__ __forceinline__ unsigned neighbour_offset(int s0, bool wrap, int L, int step, float bc)
+{
+    const unsigned o = (unsigned)(wrap ? s0 - (L - 1) * step : s0 + step) * (unsigned)RawSpinor<S>::B;
+    return wrap && bc == 0.0f ? 0x80000000u : o;
+}
+
+// Link of direction mu through plane resources; `e` is the site's byte offset
+// in a plane of elements of RawSpinor<S>::B bytes.
+template <class S, bool REC>
+__device__ __forceinline__ void load_link_buf(const S *U, int mu, int Vp, unsigned e,
+                                              cx<typename StoreT<S>::real> (&u)[3][3])
+{
+    using Raw = RawSpinor<S>;
+    const S *b = U + (size_t)(mu * 9) * (unsigned)Vp;
+    constexpr int NE = (REC ? 6 : Raw::C == 2 ? 8 : 9) / Raw::C;
+#pragma unroll
+    for (int q = 0; q < NE; ++q) {
+        uint32_t o[Raw::B / 4];
+        Raw::template ld<0>(b, Vp, q, e, o);
+#pragma unroll
+        for (int h = 0; h < Raw::C; ++h) u[(q * Raw::C + h) / 3][(q * Raw::C + h) % 3] = Raw::get(o, h);
+    }
+    if constexpr (REC) rebuild_row2(u);
+    else if constexpr (Raw::C == 2) u[2][2] = ldp<S, typename StoreT<S>::real>(b + (size_t)8 * (unsigned)Vp, e / Raw::B);
+}
+
+__device__ __forceinline__ float flip_sign(float v, uint32_t bit) { return __uint_as_float(__float_as_uint(v) ^ bit); }
+__device__ __forceinline__ double flip_sign(double v, uint32_t bit)
+{
+    return __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, v) ^ ((uint64_t)bit << 32));
 }
 
 }  // namespace ov

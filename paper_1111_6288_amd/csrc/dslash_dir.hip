@@ -39,19 +39,16 @@ struct UnitOf {
     };
 };
 
-// Unit q of a field at one site.
+// Unit q of a field at byte offset e of its plane.
 template <class S, bool NT>
-__device__ __forceinline__ typename UnitOf<S>::T ld_unit(const S *__restrict__ f, int Vp, int q, unsigned site)
+__device__ __forceinline__ typename UnitOf<S>::T ld_unit(const S *__restrict__ f, int Vp, int q, unsigned e)
 {
-    using R = typename StoreT<S>::real;
+    using Raw = RawSpinor<S>;
+    uint32_t o[Raw::B / 4];
+    Raw::template ld<NT ? 2 : 0>(f, Vp, q, e, o);
     typename UnitOf<S>::T t;
-    if constexpr (UnitOf<S>::C == 2) {
-        if constexpr (NT) ldpair_nt<S, R>(f, Vp, q, site, t.c[0], t.c[1]);
-        else ldpair<S, R>(f, Vp, q, site, t.c[0], t.c[1]);
-    } else {
-        if constexpr (NT) t.c[0] = ldp_nt<S, R>(f + (size_t)q * (unsigned)Vp, site);
-        else t.c[0] = ldp<S, R>(f + (size_t)q * (unsigned)Vp, site);
-    }
+#pragma unroll
+    for (int h = 0; h < Raw::C; ++h) t.c[h] = Raw::get(o, h);
     return t;
 }
 
@@ -70,24 +67,27 @@ __device__ __forceinline__ void st_unit(S *__restrict__ f, int Vp, int q, unsign
 
 // Both hops of direction MU at `site` (a real site): link times half spinor
 // to out[6 components at stride 64], the forward hop first, the backward hop
-// 6 x 64 behind.  A hop that leaves the lattice through a Dirichlet boundary
-// reads the wrapped site like any other and its half spinor is replaced by
-// zeros (not multiplied: the neighbour may hold infinities or NaN).
+// 6 x 64 behind.
 template <int MU, class S, bool REC>
 __device__ __forceinline__ void dir_hops(const DsArgs<S> &a, const S *__restrict__ x, int site, int cmu, int Lmu,
                                          int stride, cx<typename StoreT<S>::real> ph,
                                          cx<typename StoreT<S>::real> *__restrict__ out)
 {
     using R = typename StoreT<S>::real;
+    using Raw = RawSpinor<S>;
     const int Vp = a.g.Vp;
+    const float bc = a.g.bcf[MU];
     const bool wf = cmu == Lmu - 1, wb = cmu == 0;
-    const int jf = wf ? site - (Lmu - 1) * stride : site + stride;
-    const int jb = wb ? site + (Lmu - 1) * stride : site - stride;
+    const unsigned es = (unsigned)site * (unsigned)Raw::B;
+    const unsigned eu = (unsigned)(wb ? site + (Lmu - 1) * stride : site - stride) * (unsigned)Raw::B;
     cx<R> uf[3][3], ub[3][3], pf[4][3], pb[4][3];
-    load_link<S, R, REC>(a.U, MU, Vp, (unsigned)site, uf);
-    load_spinor<S, R>(x, Vp, (unsigned)jf, pf);
-    load_link<S, R, REC>(a.U, MU, Vp, (unsigned)jb, ub);
-    load_spinor<S, R>(x, Vp, (unsigned)jb, pb);
+    Raw rf, rb;
+    rf.load(x, Vp, neighbour_offset<S>(site, wf, Lmu, stride, bc));
+    rb.load(x, Vp, neighbour_offset<S>(site, wb, Lmu, -stride, bc));
+    load_link_buf<S, REC>(a.U, MU, Vp, es, uf);
+    load_link_buf<S, REC>(a.U, MU, Vp, eu, ub);
+    rf.spinor(pf);
+    rb.spinor(pb);
     cx<R> hf[2][3], hb[2][3];
     project<MU, -1>(pf, hf);
     project<MU, +1>(pb, hb);
@@ -100,16 +100,14 @@ __device__ __forceinline__ void dir_hops(const DsArgs<S> &a, const S *__restrict
                 hb[k][c] = phase_mul<S>(cmk(ph.x, -ph.y), hb[k][c], k, c, a.n == 1);
             }
     }
-    if (__any(wf || wb)) {
-        const R bc = (R)a.g.bcf[MU];
-        const R sf = wf ? bc : (R)1, sb = wb ? bc : (R)1;
-        const bool zf = sf == (R)0, zb = sb == (R)0;
+    if (bc < 0.0f) {   // antiperiodic
+        const uint32_t ff = wf ? 0x80000000u : 0u, fb = wb ? 0x80000000u : 0u;
 #pragma unroll
         for (int k = 0; k < 2; ++k)
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                hf[k][c] = zf ? cmk((R)0, (R)0) : cscale(hf[k][c], sf);
-                hb[k][c] = zb ? cmk((R)0, (R)0) : cscale(hb[k][c], sb);
+                hf[k][c] = cmk(flip_sign(hf[k][c].x, ff), flip_sign(hf[k][c].y, ff));
+                hb[k][c] = cmk(flip_sign(hb[k][c].x, fb), flip_sign(hb[k][c].y, fb));
             }
     }
 #pragma unroll
@@ -173,7 +171,7 @@ __global__ __launch_bounds__(256, 2) void k_dslash_dir(DsArgs<S> a)
     int site;
     if (a.order == 1 || a.order == 3) site = slab_site(g, a.order, a.cols, xcd, (int)blockIdx.y * 64 + lane);
     else site = (xcd * (int)gridDim.y + (int)blockIdx.y) * 64 + lane;
-    const int s = a.slots ? a.slots[j] : j;
+    const int s = __builtin_amdgcn_readfirstlane(a.slots ? a.slots[j] : j);
     const size_t off = (size_t)s * (size_t)a.fstride;
     const S *x = a.x + off;
 
@@ -191,11 +189,11 @@ __global__ __launch_bounds__(256, 2) void k_dslash_dir(DsArgs<S> a)
 #pragma unroll
     for (int i = 0; i < NMINE; ++i) {
         const int q = i < nmine ? q0 + i : q0;
-        own[i] = ld_unit<S, false>(x, Vp, q, (unsigned)s0);
+        own[i] = ld_unit<S, false>(x, Vp, q, (unsigned)s0 * (unsigned)RawSpinor<S>::B);
         if constexpr (EPI) {
 #pragma unroll
             for (int t = 0; t < 3; ++t)
-                if (e[t]) ep[t][i] = ld_unit<S, NT>(e[t] + off, Vp, q, (unsigned)s0);
+                if (e[t]) ep[t][i] = ld_unit<S, NT>(e[t] + off, Vp, q, (unsigned)s0 * (unsigned)RawSpinor<S>::B);
         }
     }
     cx<R> *out = hop + wave * 12 * 64 + lane;

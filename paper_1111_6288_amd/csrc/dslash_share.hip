@@ -26,56 +26,6 @@
 
 namespace ov {
 
-// One spinor as loaded, by buffer instructions: the plane is a scalar
-// resource and the site a 32-bit lane offset, so a load costs no vector
-// address arithmetic (with 64-bit lane addresses every load takes a 64-bit
-// add).  A resource covers exactly one plane.
-template <class S>
-struct RawSpinor {
-    using R = typename StoreT<S>::real;
-    static constexpr int C = Pair<S>::E, N = 12 / C, B = C * (int)sizeof(S);   // bytes of an element
-    uint32_t w[N][B / 4];
-
-    static __device__ __forceinline__ __amdgpu_buffer_rsrc_t plane(const S *f, int Vp, int q)
-    {
-        return __builtin_amdgcn_make_buffer_rsrc((void *)(f + (size_t)(q * C) * (unsigned)Vp), 0, (unsigned)Vp * B,
-                                                 0x00020000);
-    }
-    template <int AUX>
-    static __device__ __forceinline__ void ld(const S *f, int Vp, int q, unsigned boff, uint32_t (&o)[B / 4])
-    {
-        if constexpr (B == 16) {
-            const auto v = __builtin_amdgcn_raw_buffer_load_b128(plane(f, Vp, q), boff, 0, AUX);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) o[i] = v[i];
-        } else {
-            o[0] = __builtin_amdgcn_raw_buffer_load_b32(plane(f, Vp, q), boff, 0, AUX);
-        }
-    }
-    // component h of an element
-    static __device__ __forceinline__ cx<R> get(const uint32_t (&o)[B / 4], int h)
-    {
-        if constexpr (sizeof(S) == 16) {
-            return cmk(__builtin_bit_cast(double, (uint64_t)o[0] | ((uint64_t)o[1] << 32)),
-                       __builtin_bit_cast(double, (uint64_t)o[2] | ((uint64_t)o[3] << 32)));
-        } else if constexpr (sizeof(S) == 8) {
-            return cmk(__uint_as_float(o[2 * h]), __uint_as_float(o[2 * h + 1]));
-        } else {
-            return cmk(bf16_lo(o[0]), bf16_hi(o[0]));
-        }
-    }
-    __device__ __forceinline__ void load(const S *f, int Vp, unsigned boff)
-    {
-#pragma unroll
-        for (int q = 0; q < N; ++q) ld<0>(f, Vp, q, boff, w[q]);
-    }
-    __device__ __forceinline__ void spinor(cx<R> (&p)[4][3]) const
-    {
-#pragma unroll
-        for (int k = 0; k < 12; ++k) p[k / 3][k % 3] = get(w[k / C], k % C);
-    }
-};
-
 // The sums are final here: keeps the compiler from putting off the arithmetic
 // of a hop, with its links and neighbour held in registers, behind the loads
 // of the next.
@@ -86,12 +36,6 @@ __device__ __forceinline__ void settle(cx<R> (&acc)[4][3])
     for (int sp = 0; sp < 4; ++sp)
         asm volatile("" : "+v"(acc[sp][0].x), "+v"(acc[sp][0].y), "+v"(acc[sp][1].x), "+v"(acc[sp][1].y),
                           "+v"(acc[sp][2].x), "+v"(acc[sp][2].y));
-}
-
-__device__ __forceinline__ float flip_sign(float v, uint32_t bit) { return __uint_as_float(__float_as_uint(v) ^ bit); }
-__device__ __forceinline__ double flip_sign(double v, uint32_t bit)
-{
-    return __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, v) ^ ((uint64_t)bit << 32));
 }
 
 // acc += hop H (2 mu: forward, 2 mu + 1: backward) of the neighbour `raw`.
@@ -176,15 +120,11 @@ __global__ __launch_bounds__(512, sizeof(S) == 16 ? 2 : 4) void k_dslash_share(D
     const size_t off = (size_t)s * (size_t)a.fstride;
     const S *x = a.x + off;
     const bool wr[8] = {xc == g.Lx - 1, xc == 0, yc == g.Ly - 1, yc == 0, zc == g.Lz - 1, zc == 0, tc == g.Lt - 1, tc == 0};
-    // byte offset of the neighbour of hop h inside a plane; across a Dirichlet boundary one beyond
-    // every plane, which a buffer load answers with zeros
     auto nb = [&](int h) {
         const int mu = h / 2;
         const int st = mu == 0 ? 1 : mu == 1 ? g.Lx : mu == 2 ? g.Lxy : g.Lxyz;
         const int L = mu == 0 ? g.Lx : mu == 1 ? g.Ly : mu == 2 ? g.Lz : g.Lt;
-        const int step = h % 2 ? -st : st;
-        const unsigned o = (unsigned)(wr[h] ? s0 - (L - 1) * step : s0 + step) * (unsigned)Raw::B;
-        return wr[h] && g.bcf[mu] == 0.0f ? 0x80000000u : o;
+        return neighbour_offset<S>(s0, wr[h], L, h % 2 ? -st : st, g.bcf[mu]);
     };
     auto flip = [&](int h) { return wr[h] && g.bcf[h / 2] < 0.0f ? 0x80000000u : 0u; };
     const int grp = __builtin_amdgcn_readfirstlane(a.fgroup ? a.fgroup[s] : 0);

@@ -250,6 +250,22 @@ struct Geo {
     int V, Vp;
     int Lxy, Lxyz;
     float bcf[4];   // boundary multiplier on wrapping hops: 1, -1 or 0
+    uint32_t mul[3], shr[3];   // site / L for Lx, Ly, Lz as a product: see set_divisors
 };
+
+// n / L = (n mul) >> (32 + shr) for every site index n < 2^25 and 2 <= L <=
+// 4096: with mul = floor(2^(32 + shr) / L) + 1 the quotient is exact while
+// n L < 2^(32 + shr), which shr = max(0, ceil(log2 L) - 7) ensures (and mul
+// fits 32 bits because 2^shr < L).
+inline void set_divisors(Geo &g)
+{
+    const int L[3] = {g.Lx, g.Ly, g.Lz};
+    for (int i = 0; i < 3; ++i) {
+        int lg = 0;
+        while ((1 << lg) < L[i]) ++lg;
+        g.shr[i] = lg > 7 ? lg - 7 : 0;
+        g.mul[i] = (uint32_t)((1ull << (32 + g.shr[i])) / (unsigned)L[i]) + 1u;
+    }
+}
 
 }  // namespace ov
