@@ -442,44 +442,52 @@ const uint32_t *links_of<uint32_t>(const ov_ctx *c) { return c->U16; }
 // (an empty node takes 1.6 us).
 //
 // Direction waves for small batches, which wait for memory latency, not bandwidth: FP64 12 RHS of
-// 4^4 16.7 (two RHS per thread) -> 5.1 us, FP32 4 RHS of 8^3x16 16.3 -> 6.7 us.  Every right-hand
-// side reads all eight links and rebuilds their third rows, so a batch gains until its fields
-// outgrow the caches and sharing staged links wins (12 RHS FP64: 12^3x24, F = 96 MB, 96 us against
-// 100; 16^3x32, 302 MB, 336 against 301).  Up to three vectors gain on the largest lattice too
-// (one of 24^3x48: FP64 222 -> 157 us, FP32 96 -> 70).  BF16 halves the bytes but not the
-// arithmetic: 12 RHS of 8^3x16, 4.7 MB, 11.8 against 12.4 us, 4 RHS of 12^3x24, 8 MB, 17.2
-// against 16.3.
+// 4^4 16.7 (two RHS per thread) -> 5.1 us, FP32 4 RHS of 8^3x16 16.3 -> 6.6 us.  Every right-hand
+// side reads all eight links and rebuilds their third rows, so sharing staged links wins once the
+// fields outgrow the caches or, in FP64, the batch is long.  Direction waves / shared links:
+//   FP64 6x5x7x10 12 RHS (5 MB) 8.7 / 12.2 us, 12^3x24 6 RHS (48 MB) 43.7 / 46.0, 8 RHS 58.8 / 59.8, 12 RHS (96 MB) 94 / 88,
+//        8^3x16 8 RHS 14.3 / 14.1, 24 RHS (38 MB) 35.7 / 33.0, 16^3x32 2 RHS 49 / 49, 4 RHS 102 / 95;
+//   FP32 12^3x24 8 RHS (32 MB) 28.3 / 29.6, 12 RHS (48 MB) 41.1 / 40.2, 16^3x32 6 RHS (75 MB) 77 / 69;
+//   BF16 12^3x24 3 RHS (6 MB) 12.7 / 14.2, 4 RHS (8 MB) 16.0 / 15.3, 16^3x32 2 RHS (13 MB) 22.9 / 25.7.
+// One or two vectors gain on the largest lattice too (one of 24^3x48: FP64 222 -> 157 us, FP32
+// 96 -> 70), except in BF16 (one thread for both 48 us, direction waves 56).
 //
-// Link sharing otherwise: the W waves of a workgroup hold W right-hand sides of the same sites.
-// W = 8, or the even split when more than half of a workgroup would idle (24^3x48 FP32: 12 RHS W 8
-// 719 us, W 6 739, W 4 754, two RHS per thread 1121; 9 RHS W 8 623, W 5 560; BF16 12 RHS W 8 470,
-// W 4 490, two per thread 554).  FP64 stages twice the bytes: W up to 4, split evenly (12 RHS W 4
-// 1511, W 8 1607, two per thread 2459; 5 RHS W 3 681, W 4 734).  BF16 with one or two vectors
-// keeps one thread for all of them (24^3x48, one vector: 48 us, direction waves 56).
+// Link sharing: the W waves of a workgroup hold W right-hand sides of the same sites.  W = 8, or the
+// even split of a batch that would leave more than half of a workgroup idle (24^3x48 FP32: 12 RHS
+// W 8 719 us, W 6 739, W 4 754, two RHS per thread 1121; 9 RHS W 8 623, W 5 560; BF16 12 RHS W 8
+// 470, W 4 490, two per thread 554).  FP64 stages twice the bytes: W up to 4, split evenly (12 RHS
+// W 4 1511, W 8 1607, two per thread 2459; 5 RHS W 3 681, W 4 734).
 //
-// Site order: from F = 64 MB on z-slabs per XCD (t-slabs where Lz % 8), non-temporal own-site
-// streams (24^3x48 FP64 one vector: canonical order 175, z-slabs 164, with the hint 157); between
-// 16 and 64 MB t-slabs, which the caches still hold (16^3x32 FP64: 31.2 -> 28.4, z-slabs 29.9,
-// with the hint 31.0); below, canonical order.
+// Site order and streams: large batches walk z-slabs per XCD (t-slabs where Lz % 8) with
+// non-temporal own-site streams (24^3x48 FP64 one vector: canonical order 175, z-slabs 164, with
+// the hint 157; 16^3x32 FP32 8 RHS, 100 MB: t-slabs 96.8, z-slabs with the hint 91.6).  What the
+// caches still hold between launches takes t-slabs without the hint (16^3x32 FP64 one vector
+// 31.2 -> 28.4, with the hint 31.0; FP32 6 RHS, 75 MB, 70.6 against 73.5), BF16 canonical order
+// (16^3x32 12 RHS 92 us, z-slabs with the hint 103).
 template <class S>
 ov_ctx::Launch launch_rule(const Geo &g, int n)
 {
     ov_ctx::Launch t;
+    constexpr bool f64 = sizeof(S) == 16, bf16 = sizeof(S) == 4;
     const double F = 12.0 * sizeof(S) * g.V * n;
     const bool zslab = g.Lz % 8 == 0 && g.V % 64 == 0, tslab = g.Lt % 8 == 0 && g.V % 64 == 0;
-    const bool bf16 = sizeof(S) == 4;
     t.nr = 1;
-    t.dir = (bf16 ? F <= 7e6 : n <= 3 || F <= 96e6) && dslash_dir_fits(g);
-    t.stream_hint = F > 64e6 ? 1 : 0;
-    if (t.dir) {
-        t.order = F > 64e6 && zslab ? 1 : F > 16e6 && F <= 64e6 && tslab ? 3 : 0;
-    } else {
-        t.order = zslab ? 1 : tslab ? 3 : 0;
-        const int most = sizeof(S) == 16 ? 4 : 8, groups = (n + most - 1) / most;
-        const bool full = sizeof(S) != 16 && 2 * (most * groups - n) <= most;
-        if (bf16 && n <= 2) t.nr = 2;
-        else t.wshare = full ? most : (n + groups - 1) / groups;
+    t.dir = (f64    ? n <= 2 || F <= 8e6 || (n <= 7 && F <= 64e6)
+             : bf16 ? F <= 7e6 || (n <= 2 && F <= 16e6)
+                    : n <= 2 || F <= 45e6) &&
+            dslash_dir_fits(g);
+    const bool streams = F > (t.dir || f64 ? 64e6 : bf16 ? 110e6 : 90e6);
+    t.stream_hint = streams ? 1 : 0;
+    if (streams) t.order = zslab ? 1 : tslab && !t.dir ? 3 : 0;
+    else t.order = tslab && (t.dir ? F > 16e6 : !bf16) ? 3 : 0;
+    if (t.dir) return t;
+    if (bf16 && n <= 2) {
+        t.nr = 2;
+        return t;
     }
+    const int most = f64 ? 4 : 8, groups = (n + most - 1) / most;
+    const bool full = !f64 && groups > 1 && 2 * (most * groups - n) <= most;
+    t.wshare = full ? most : (n + groups - 1) / groups;
     return t;
 }
 
