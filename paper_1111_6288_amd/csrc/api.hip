@@ -2035,15 +2035,27 @@ int api_backward(ov_ctx *c, int f, const void *x_dev, const void *g_dev, void *g
     CHK(dslash_launch<S>(c, b, fg, wbar, zbar, invN, true));
 
     HIPCHK(hipMemsetAsync(G, 0, 36ul * c->g.Vp * 16, c->stream));
-    auto force = [&](const S *u, const S *v, double coef) -> int {
-        ForceArgs fa{u, v, G, coef, c->g};
+    // terms Re<u, dQ v> are collected and added to G together
+    ForceArgs fa{};
+    fa.G = G;
+    fa.g = c->g;
+    auto flush = [&]() -> int {
+        if (fa.n == 0) return OV_OK;
         int pi = prof_begin(c);
         HIPCHK(launch_force(fa, c->stream));
-        prof_end(c, pi, PC_FORCE, (double)c->g.V * (4 * 192.0 + 2 * 576.0));
+        prof_end(c, pi, PC_FORCE, (double)c->g.V * (fa.n * 4 * 192.0 + 2 * 576.0));
+        fa.n = 0;
         return OV_OK;
+    };
+    auto force = [&](const S *u, const S *v, double coef) -> int {
+        fa.u[fa.n] = u;
+        fa.v[fa.n] = v;
+        fa.coef[fa.n] = coef;
+        return ++fa.n == kForcePairs ? flush() : OV_OK;
     };
     // Re<wbar, dQ z>
     CHK(force(wbar, z, invN));
+    CHK(flush());
 
     // adjoint vectors bb_k = T_k(T) zbar, upward; pairs with b_{k+1}
     // bb_0 = zbar (kept in bbv[0]), bb_1 = T zbar
@@ -2083,14 +2095,16 @@ int api_backward(ov_ctx *c, int f, const void *x_dev, const void *g_dev, void *g
                 const S *b1v = seg[0];
                 CHK(dslash_launch<S>(c, b, fg, b1v, t2, 1.0, true));   // N Q b_1
                 CHK(force(zbar, t2, kap * invN * invN));
-                CHK(dslash_launch<S>(c, b, fg, zbar, t2, 1.0, true));  // N Q zbar
-                CHK(force(t2, b1v, kap * invN * invN));
+                CHK(dslash_launch<S>(c, b, fg, zbar, t1, 1.0, true));  // N Q zbar
+                CHK(force(t1, b1v, kap * invN * invN));
+                CHK(flush());
             }
             // 2 Re<bb_k, dT b_{k+1}> = 2 kap (Re<bb_k, dQ Q b_{k+1}> + Re<Q bb_k, dQ b_{k+1}>)
             CHK(dslash_launch<S>(c, b, fg, bk1, t2, 1.0, true));
             CHK(force(bbv[cur], t2, 2.0 * kap * invN * invN));
             CHK(dslash_launch<S>(c, b, fg, bbv[cur], t1, 1.0, true));
             CHK(force(t1, bk1, 2.0 * kap * invN * invN));
+            CHK(flush());   // t1, t2 and bb_{k-1} are overwritten next
             // bb_{k+1} = 2T bb_k - bb_{k-1} = 2 al H t1 - 2 be bb_k - bb_{k-1}, into bb_{k-1}'s buffer
             CHK(dslash_launch<S>(c, b, fg, t1, bbv[prev], 2.0 * al, true, bbv[cur], -2.0 * be, bbv[prev], -1.0));
             std::swap(cur, prev);

@@ -114,11 +114,13 @@ hipError_t launch_small_combine(const double2 *C, const double2 *D, const double
 hipError_t launch_mul_coef(const double2 *C, const double *w, int l, int n, double2 *E, hipStream_t st);
 
 // ---------------------------------------------------------------- backward
+constexpr int kForcePairs = 4;
 struct ForceArgs {
-    const double2 *u;        // planes [12][Vp]
-    const double2 *v;        // planes [12][Vp]
-    double2 *G;              // force accumulator [4][9][Vp] (phased links)
-    double coef;             // weight of Re<u, dQ v>, includes 1/norm
+    int n;                          // terms, at most kForcePairs
+    const double2 *u[kForcePairs];  // planes [12][Vp]
+    const double2 *v[kForcePairs];  // planes [12][Vp]
+    double coef[kForcePairs];       // weight of Re<u, dQ v>, includes 1/norm
+    double2 *G;                     // force accumulator [4][9][Vp] (phased links)
     Geo g;
 };
 hipError_t launch_force(const ForceArgs &a, hipStream_t st);
