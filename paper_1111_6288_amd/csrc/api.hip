@@ -1945,16 +1945,32 @@ int api_backward(ov_ctx *c, int f, const void *x_dev, const void *g_dev, void *g
     const int nseg = (n + K - 1) / K;
     const int nb_fin = (c->g.V + 255) / 256;
     // fields: X, Gv, chi, z, wbar, zbar, t1, t2, bb[3], seg[K], ckpt[2*nseg], sign bufs
-    const size_t nf = 11 + (size_t)K + 2 * nseg;
-    const size_t need = nf * align_up(field_bytes<S>(c)) + align_up(36ul * c->g.Vp * 16) + align_up(8ul * nb_fin) +
+    const size_t fb = align_up(field_bytes<S>(c));
+    const size_t need = (11 + (size_t)K + 2 * nseg) * fb + align_up(36ul * c->g.Vp * 16) + align_up(8ul * nb_fin) +
                         sign_bufs_bytes<S>(c, 1);
-    CHK(ws_reserve(c, need));
+    // K more hold H_w b_{k+1} of a replayed segment, which the sweep needs again (n launches fewer):
+    // taken where the arena has them already or half of the free memory does
+    const size_t more = (size_t)K * fb;
+    bool keep_h = need + more <= c->ws_size;
+    if (!keep_h) {
+        size_t avail = 0, total = 0;
+        if (hipMemGetInfo(&avail, &total) != hipSuccess) avail = 0;
+        keep_h = need + more <= (avail + c->ws_size) / 2;
+    }
+    int rc = ws_reserve(c, need + (keep_h ? more : 0));
+    if (rc == OV_ENOMEM && keep_h) {
+        keep_h = false;
+        rc = ws_reserve(c, need);
+    }
+    CHK(rc);
     S *X = ws_take<S>(c, fe), *Gv = ws_take<S>(c, fe), *chi = ws_take<S>(c, fe), *z = ws_take<S>(c, fe);
     S *wbar = ws_take<S>(c, fe), *zbar = ws_take<S>(c, fe), *t1 = ws_take<S>(c, fe), *t2 = ws_take<S>(c, fe);
     S *bb[3] = {ws_take<S>(c, fe), ws_take<S>(c, fe), ws_take<S>(c, fe)};
     std::vector<S *> seg(K), ck(2 * nseg);
     for (int i = 0; i < K; ++i) seg[i] = ws_take<S>(c, fe);
     for (int i = 0; i < 2 * nseg; ++i) ck[i] = ws_take<S>(c, fe);
+    std::vector<S *> hb(keep_h ? K : 0);   // H_w b_{k+1}, k = lo + i
+    for (auto &p : hb) p = ws_take<S>(c, fe);
     double2 *G = ws_take<double2>(c, 36ul * c->g.Vp);
     double *epart = ws_take<double>(c, nb_fin);
     SignBufs<S> w;
@@ -1987,8 +2003,8 @@ int api_backward(ov_ctx *c, int f, const void *x_dev, const void *g_dev, void *g
     } else {
         CHK((copy_fields<S, S>(c, b, X, chi)));
     }
-    // One Clenshaw step k: out = c_k chi + 2T b1 - b2 (b2 may be NULL); uses t1.
-    auto step = [&](int k, const S *b1, const S *b2, S *out) -> int {
+    // One Clenshaw step k: out = c_k chi + 2T b1 - b2 (b2 may be NULL); h = H_w b1.
+    auto step = [&](int k, const S *b1, const S *b2, S *out, S *h) -> int {
         if (k == n) {
             const S *in[1] = {chi};
             const double2 cc[1] = {make_double2(c->coef[n], 0)};
@@ -2014,7 +2030,7 @@ int api_backward(ov_ctx *c, int f, const void *x_dev, const void *g_dev, void *g
             }
             S *out = bb[i1];
             if (b2 == bb[0] || b2 == bb[1] || b2 == bb[2]) out = (S *)b2;
-            CHK(step(k, b1, b2, out));
+            CHK(step(k, b1, b2, out, t1));
             b2 = b1;
             b1 = out;
             i1 = (out == bb[0]) ? 1 : (out == bb[1] ? 2 : 0);
@@ -2076,11 +2092,12 @@ int api_backward(ov_ctx *c, int f, const void *x_dev, const void *g_dev, void *g
             const bool fresh = (top == n);
             for (int k = top; k >= lo; --k) {
                 S *out = seg[k - lo];
+                S *h = keep_h ? hb[k - lo] : t1;
                 if (k == n) {
-                    CHK(step(k, nullptr, nullptr, out));
+                    CHK(step(k, nullptr, nullptr, out, h));
                 } else {
                     const bool b2zero = fresh && (k == n - 1);
-                    CHK(step(k, b1, b2zero ? nullptr : b2, out));
+                    CHK(step(k, b1, b2zero ? nullptr : b2, out, h));
                 }
                 b2 = b1;
                 b1 = out;
@@ -2100,8 +2117,9 @@ int api_backward(ov_ctx *c, int f, const void *x_dev, const void *g_dev, void *g
                 CHK(flush());
             }
             // 2 Re<bb_k, dT b_{k+1}> = 2 kap (Re<bb_k, dQ Q b_{k+1}> + Re<Q bb_k, dQ b_{k+1}>)
-            CHK(dslash_launch<S>(c, b, fg, bk1, t2, 1.0, true));
-            CHK(force(bbv[cur], t2, 2.0 * kap * invN * invN));
+            const S *hk = keep_h ? hb[k - lo] : t2;   // N Q b_{k+1}
+            if (!keep_h) CHK(dslash_launch<S>(c, b, fg, bk1, t2, 1.0, true));
+            CHK(force(bbv[cur], hk, 2.0 * kap * invN * invN));
             CHK(dslash_launch<S>(c, b, fg, bbv[cur], t1, 1.0, true));
             CHK(force(t1, bk1, 2.0 * kap * invN * invN));
             CHK(flush());   // t1, t2 and bb_{k-1} are overwritten next
