@@ -131,8 +131,7 @@ struct ov_ctx {
     size_t ev_used = 0;
     std::vector<ProfRec> recs;
 
-    // persistent small device scratch: [0] non-finite count, [8] row-3 deviation bits,
-    // [16] norm-breach flag, [32..63] link rounding deviation bits
+    // persistent small device scratch: [0] non-finite count, [16] norm-breach flag, [64] LinkScan
     int *d_count = nullptr;
 
     // pinned host words for the lagged reads of the CG's active flags
@@ -1208,32 +1207,24 @@ int ov_upload_gauge(ov_ctx *c, const void *U_dev)
     OV_RANGE("ov_upload_gauge");
     CHK(check_ctx(c));
     if (!U_dev) return fail(c, OV_EINVAL, "null gauge pointer");
-    int bad = 0;
-    CHK(count_nonfinite(c, U_dev, 4L * c->g.V * 18, &bad));
-    if (bad) return fail(c, OV_ENAN, "gauge field holds %d non-finite numbers", bad);
+    // one read-only pass measures the links, so a bad field leaves the context's links alone
+    LinkScan h{}, *scan = (LinkScan *)((char *)c->d_count + 64);
+    HIPCHK(hipMemsetAsync(scan, 0, sizeof h, c->stream));
+    HIPCHK(launch_scan_links((const double2 *)U_dev, c->g.V, scan, c->stream));
+    HIPCHK(hipMemcpyAsync(&h, scan, sizeof h, hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(hipStreamSynchronize(c->stream));
+    if (h.nonfinite) return fail(c, OV_ENAN, "gauge field holds %d non-finite numbers", h.nonfinite);
     const size_t n = 36ul * c->g.Vp;
     if (!c->U64) {
         CHK(dev_alloc(c, (void **)&c->U64, n * sizeof(double2)));
         CHK(dev_alloc(c, (void **)&c->U32, n * sizeof(float2)));
         CHK(dev_alloc(c, (void **)&c->U16, n * sizeof(uint32_t)));
     }
-    HIPCHK(launch_pack_links<double2>((const double2 *)U_dev, c->U64, c->g.V, c->g.Vp, c->stream));
-    HIPCHK(launch_pack_links<float2>((const double2 *)U_dev, c->U32, c->g.V, c->g.Vp, c->stream));
-    HIPCHK(launch_pack_links<uint32_t>((const double2 *)U_dev, c->U16, c->g.V, c->g.Vp, c->stream));
-    unsigned long long *d_dev = (unsigned long long *)((char *)c->d_count + 8);
-    unsigned long long dev_bits = 0;
-    HIPCHK(hipMemsetAsync(d_dev, 0, sizeof(dev_bits), c->stream));
-    HIPCHK(launch_link_row3_dev((const double2 *)U_dev, 4L * c->g.V, d_dev, c->stream));
-    HIPCHK(hipMemcpyAsync(&dev_bits, d_dev, sizeof(dev_bits), hipMemcpyDeviceToHost, c->stream));
-    unsigned long long *rd_dev = (unsigned long long *)((char *)c->d_count + 32);
-    unsigned long long rd_bits[4] = {0, 0, 0, 0};
-    HIPCHK(hipMemsetAsync(rd_dev, 0, sizeof(rd_bits), c->stream));
-    HIPCHK(launch_link_round_dev((const double2 *)U_dev, 4L * c->g.V, rd_dev, c->stream));
-    HIPCHK(hipMemcpyAsync(rd_bits, rd_dev, sizeof(rd_bits), hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(launch_pack_links((const double2 *)U_dev, c->U64, c->U32, c->U16, c->g.V, c->g.Vp, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
-    std::memcpy(&c->row3_dev, &dev_bits, sizeof(double));
+    std::memcpy(&c->row3_dev, &h.row3, sizeof(double));
     for (int p = 0; p < 2; ++p)
-        for (int r = 0; r < 2; ++r) std::memcpy(&c->link_dev[1 + p][r], &rd_bits[2 * p + r], sizeof(double));
+        for (int r = 0; r < 2; ++r) std::memcpy(&c->link_dev[1 + p][r], &h.round[2 * p + r], sizeof(double));
     invalidate_graphs(c);   // the FP32 / BF16 norms baked into captured pipelines may change
     c->have_gauge = true;
     update_link_format(c);
@@ -2010,8 +2001,8 @@ int api_backward(ov_ctx *c, int f, const void *x_dev, const void *g_dev, void *g
             const double2 cc[1] = {make_double2(c->coef[n], 0)};
             return lincomb<S, S>(c, b, out, 1, in, nullptr, cc, 0);
         }
-        CHK(dslash_launch<S>(c, b, fg, b1, t1, 1.0, true));
-        return dslash_launch<S>(c, b, fg, t1, out, 2.0 * al, true, chi, c->coef[k], b1, -2.0 * be, b2, -1.0);
+        CHK(dslash_launch<S>(c, b, fg, b1, h, 1.0, true));
+        return dslash_launch<S>(c, b, fg, h, out, 2.0 * al, true, chi, c->coef[k], b1, -2.0 * be, b2, -1.0);
     };
     // forward pass: keep (b_{top+1}, b_{top+2}) of every segment [s*K+1, min((s+1)K, n)]
     {

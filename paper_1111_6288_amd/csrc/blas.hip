@@ -109,21 +109,38 @@ __global__ __launch_bounds__(256) void k_unpack_spinor(const S *__restrict__ in,
     }
 }
 
-// canonical [4][V][3][3]  ->  internal link layout
-template <class S>
-__global__ void k_pack_links(const double2 *__restrict__ in, S *__restrict__ out, int V, int Vp)
+// The link of (mu, site) of canonical [4][V][3][3] into registers: a wave reads its 64 consecutive
+// links, 9 KiB, as nine runs of 64 numbers and hands them out through LDS (9 x 16 bytes a row: an odd
+// number of 16-byte elements, so no two of 16 lanes meet in a bank).  Every thread of the workgroup
+// must call it; sites from V on give zeros.
+__device__ __forceinline__ void wave_links(const double2 *__restrict__ U, int mu, int base, int V,
+                                           double2 (*sh)[64 * 9], double2 (&m)[9])
 {
-    const int site = blockIdx.x * blockDim.x + threadIdx.x;
-    const int mu = blockIdx.y;
-    if (site >= Vp) return;
+    const int lane = (int)(threadIdx.x & 63), wave = (int)(threadIdx.x >> 6);
+    const int nin = base < V ? (V - base < 64 ? V - base : 64) * 9 : 0;
+    const double2 *src = U + ((long)mu * V + base) * 9;
+#pragma unroll
+    for (int r = 0; r < 9; ++r) sh[wave][lane + 64 * r] = lane + 64 * r < nin ? src[lane + 64 * r] : make_double2(0.0, 0.0);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 9; ++k) m[k] = sh[wave][lane * 9 + k];
+}
+
+// canonical [4][V][3][3]  ->  the three internal link layouts, one direction per wave
+__global__ __launch_bounds__(256) void k_pack_links(const double2 *__restrict__ in, double2 *__restrict__ o64,
+                                                    float2 *__restrict__ o32, uint32_t *__restrict__ o16, int V, int Vp)
+{
+    __shared__ double2 sh[4][64 * 9];
+    const int base = blockIdx.x * 64, mu = (int)(threadIdx.x >> 6);
+    const long site = base + (int)(threadIdx.x & 63);   // < Vp, a multiple of 64
+    double2 m[9];
+    wave_links(in, mu, base, V, sh, m);
 #pragma unroll
     for (int k = 0; k < 9; ++k) {
-        cx<double> v = {0.0, 0.0};
-        if (site < V) {
-            double2 w = in[((long)mu * V + site) * 9 + k];
-            v = {w.x, w.y};
-        }
-        stc<double>(out, lpos<S>(mu, k, site, Vp), v);
+        const cx<double> v = {m[k].x, m[k].y};
+        stc<double>(o64, lpos<double2>(mu, k, site, Vp), v);
+        stc<double>(o32, lpos<float2>(mu, k, site, Vp), v);
+        stc<double>(o16, lpos<uint32_t>(mu, k, site, Vp), v);
     }
 }
 
@@ -186,38 +203,14 @@ __global__ void k_count_nonfinite(const double *__restrict__ p, long n, int *cou
     if (bad) atomicAdd(count, bad);
 }
 
-// How far each link is from the SU(3) identity u_2 = conj(u_0 x u_1) (rows
-// u_0, u_1, u_2, cross product over the colour index), in FP64.  One wave
-// reduces its lanes before the atomic.  Non-negative doubles order like their
-// bit patterns, so an unsigned 64-bit max is a max of the values.
-__global__ __launch_bounds__(256) void k_link_row3_dev(const double2 *__restrict__ U, long nl,
-                                                       unsigned long long *out)
-{
-    double worst = 0;
-    for (long l = blockIdx.x * (long)blockDim.x + threadIdx.x; l < nl; l += (long)gridDim.x * blockDim.x) {
-        const double2 *m = U + 9 * l;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const int b = (a + 1) % 3, c = (a + 2) % 3;
-            const double2 p = m[b], q = m[3 + c], r = m[c], s = m[3 + b];
-            const double tr = (p.x * q.x - p.y * q.y) - (r.x * s.x - r.y * s.y);
-            const double ti = (p.x * q.y + p.y * q.x) - (r.x * s.y + r.y * s.x);
-            const double dr = m[6 + a].x - tr, di = m[6 + a].y + ti;
-            worst = fmax(worst, sqrt(dr * dr + di * di));
-        }
-    }
-    for (int w = 32; w >= 1; w >>= 1) worst = fmax(worst, __shfl_xor(worst, w, 64));
-    if ((threadIdx.x & 63) == 0) atomicMax(out, (unsigned long long)__double_as_longlong(worst));
-}
-
 // How far the links that the FP32 and BF16 kernels apply are from the
-// uploaded FP64 links: out[2 p + r] = max over links of the Frobenius norm of
+// uploaded FP64 links: round[2 p + r] = max over links of the Frobenius norm of
 // U_eff - U for p = 0 (FP32 storage), 1 (BF16 storage) and r = 0 (nine
 // entries read), 1 (rows 0, 1 read, row 2 rebuilt as conj(u_0 x u_1)).  The
 // stored entries are rounded exactly as the packing kernel rounds them; the
 // rebuild is evaluated in FP64 here (the kernels' FP32 evaluation adds at
 // most a few FP32 ulps, which the caller allows for).  Since the Frobenius
-// norm bounds the spectral one, ||H_w(U_eff)|| <= ||H_w(U)|| + 4 out[.].
+// norm bounds the spectral one, ||H_w(U_eff)|| <= ||H_w(U)|| + 4 round[.].
 __device__ __forceinline__ double2 round_store(double2 v, int p)
 {
     if (p == 0) return make_double2((double)(float)v.x, (double)(float)v.y);
@@ -225,12 +218,31 @@ __device__ __forceinline__ double2 round_store(double2 v, int p)
     return make_double2((double)bf16_lo(w), (double)bf16_hi(w));
 }
 
-__global__ __launch_bounds__(256) void k_link_round_dev(const double2 *__restrict__ U, long nl,
-                                                        unsigned long long *out)
+// One pass over the links, a direction per wave: non-finite numbers, the distance of each link from
+// the SU(3) identity u_2 = conj(u_0 x u_1) (rows u_0, u_1, u_2, cross product over the colour index),
+// and the rounding distances above, all in FP64.  Non-negative doubles order like their bit patterns,
+// so an unsigned 64-bit max is a max of the values.  Three kernels that read 144 bytes per lane at
+// stride 144 took 22 + 99 + 380 us on 16^3x32.
+__global__ __launch_bounds__(256) void k_scan_links(const double2 *__restrict__ U, int V, int nblk, LinkScan *out)
 {
-    double worst[4] = {0, 0, 0, 0};
-    for (long l = blockIdx.x * (long)blockDim.x + threadIdx.x; l < nl; l += (long)gridDim.x * blockDim.x) {
-        const double2 *m = U + 9 * l;
+    __shared__ double2 sh[4][64 * 9];
+    int bad = 0;
+    double row3 = 0, worst[4] = {0, 0, 0, 0};
+    for (int blk = blockIdx.x; blk < nblk; blk += gridDim.x) {
+        double2 m[9];
+        wave_links(U, (int)(threadIdx.x >> 6), blk * 64, V, sh, m);
+        __syncthreads();   // the next block's links may take the place of these
+#pragma unroll
+        for (int k = 0; k < 9; ++k) bad += !isfinite(m[k].x) + !isfinite(m[k].y);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const int b = (a + 1) % 3, c = (a + 2) % 3;
+            const double2 p = m[b], q = m[3 + c], r = m[c], s = m[3 + b];
+            const double tr = (p.x * q.x - p.y * q.y) - (r.x * s.x - r.y * s.y);
+            const double ti = (p.x * q.y + p.y * q.x) - (r.x * s.y + r.y * s.x);
+            const double dr = m[6 + a].x - tr, di = m[6 + a].y + ti;
+            row3 = fmax(row3, sqrt(dr * dr + di * di));
+        }
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
             double2 r[9];
@@ -257,20 +269,31 @@ __global__ __launch_bounds__(256) void k_link_round_dev(const double2 *__restric
             worst[2 * p + 1] = fmax(worst[2 * p + 1], sqrt(top + reb));
         }
     }
+    double mx[5] = {row3, worst[0], worst[1], worst[2], worst[3]};
+    for (int w = 32; w >= 1; w >>= 1) {
+        bad += __shfl_xor(bad, w, 64);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        double v = worst[i];
-        for (int w = 32; w >= 1; w >>= 1) v = fmax(v, __shfl_xor(v, w, 64));
-        if ((threadIdx.x & 63) == 0) atomicMax(out + i, (unsigned long long)__double_as_longlong(v));
+        for (int i = 0; i < 5; ++i) mx[i] = fmax(mx[i], __shfl_xor(mx[i], w, 64));
+    }
+    // one thread per workgroup and maximum: atomics on one line are served one after the other
+    __shared__ double wmx[4][5];
+    if ((threadIdx.x & 63) == 0) {
+        if (bad) atomicAdd(&out->nonfinite, bad);
+#pragma unroll
+        for (int i = 0; i < 5; ++i) wmx[threadIdx.x >> 6][i] = mx[i];
+    }
+    __syncthreads();
+    const int i = (int)threadIdx.x;
+    if (i < 5) {
+        const double v = fmax(fmax(wmx[0][i], wmx[1][i]), fmax(wmx[2][i], wmx[3][i]));
+        atomicMax(i == 0 ? &out->row3 : &out->round[i - 1], (unsigned long long)__double_as_longlong(v));
     }
 }
 
-hipError_t launch_link_round_dev(const double2 *U, long nl, unsigned long long *out, hipStream_t st)
+hipError_t launch_scan_links(const double2 *U, int V, LinkScan *out, hipStream_t st)
 {
-    long nb = (nl + 255) / 256;
-    if (nb > 4096) nb = 4096;
-    if (nb < 1) nb = 1;
-    hipLaunchKernelGGL(k_link_round_dev, dim3(nb), dim3(256), 0, st, U, nl, out);
+    const int nblk = (V + 63) / 64;
+    hipLaunchKernelGGL(k_scan_links, dim3(std::min(nblk, 512)), dim3(256), 0, st, U, V, nblk, out);
     return hipGetLastError();
 }
 
@@ -471,11 +494,10 @@ hipError_t launch_unpack_spinor(const S *in, double2 *out, long fstride, const i
     return hipGetLastError();
 }
 
-template <class S>
-hipError_t launch_pack_links(const double2 *in, S *out, int V, int Vp, hipStream_t st)
+hipError_t launch_pack_links(const double2 *in, double2 *o64, float2 *o32, uint32_t *o16, int V, int Vp,
+                             hipStream_t st)
 {
-    dim3 grid((Vp + 255) / 256, 4);
-    hipLaunchKernelGGL((k_pack_links<S>), grid, dim3(256), 0, st, in, out, V, Vp);
+    hipLaunchKernelGGL(k_pack_links, dim3(Vp / 64), dim3(256), 0, st, in, o64, o32, o16, V, Vp);
     return hipGetLastError();
 }
 
@@ -498,15 +520,6 @@ hipError_t launch_count_nonfinite(const double *p, long n, int *count, hipStream
     if (nb > 4096) nb = 4096;
     if (nb < 1) nb = 1;
     hipLaunchKernelGGL(k_count_nonfinite, dim3(nb), dim3(256), 0, st, p, n, count);
-    return hipGetLastError();
-}
-
-hipError_t launch_link_row3_dev(const double2 *U, long nl, unsigned long long *out, hipStream_t st)
-{
-    long nb = (nl + 255) / 256;
-    if (nb > 4096) nb = 4096;
-    if (nb < 1) nb = 1;
-    hipLaunchKernelGGL(k_link_row3_dev, dim3(nb), dim3(256), 0, st, U, nl, out);
     return hipGetLastError();
 }
 
@@ -580,8 +593,7 @@ hipError_t launch_sum_rows(const double *part, int n, int Lt, double *G, hipStre
     template hipError_t launch_pack_spinor<S>(const double2 *, S *, long, const int *, int, int, int,  \
                                               hipStream_t);                                            \
     template hipError_t launch_unpack_spinor<S>(const S *, double2 *, long, const int *, int, int, int, \
-                                                hipStream_t);                                          \
-    template hipError_t launch_pack_links<S>(const double2 *, S *, int, int, hipStream_t);
+                                                hipStream_t);
 OV_INST_S(double2)
 OV_INST_S(float2)
 OV_INST_S(uint32_t)

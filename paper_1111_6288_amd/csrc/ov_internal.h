@@ -88,17 +88,20 @@ hipError_t launch_pack_spinor(const double2 *in, S *out, long fstride, const int
 template <class S>
 hipError_t launch_unpack_spinor(const S *in, double2 *out, long fstride, const int *slots, int n, int V, int Vp,
                                 hipStream_t st);
-template <class S>
-hipError_t launch_pack_links(const double2 *in, S *out, int V, int Vp, hipStream_t st);
+// canonical [4][V][3][3] to the three link layouts
+hipError_t launch_pack_links(const double2 *in, double2 *o64, float2 *o32, uint32_t *o16, int V, int Vp,
+                             hipStream_t st);
 hipError_t launch_count_nonfinite(const double *p, long n, int *count, hipStream_t st);
-// max over the nl links of canonical complex128 [nl][3][3] of
-// max_a |u_2a - conj(u_0b u_1c - u_0c u_1b)|, as the bits of a non-negative
-// double atomically maxed into *out (which the caller clears).
-hipError_t launch_link_row3_dev(const double2 *U, long nl, unsigned long long *out, hipStream_t st);
-// out[2 p + r]: max Frobenius distance between the stored links and the links
-// the kernels apply for p = 0 FP32 / 1 BF16 storage, r = 0 nine entries /
-// 1 two rows and the rebuilt third; maxed atomically (caller clears).
-hipError_t launch_link_round_dev(const double2 *U, long nl, unsigned long long *out, hipStream_t st);
+// What ov_upload_gauge asks of a field of links; maxima as the bits of
+// non-negative doubles, maxed atomically (the caller clears).
+struct LinkScan {
+    int nonfinite, pad;
+    unsigned long long row3;       // max_a |u_2a - conj(u_0b u_1c - u_0c u_1b)|
+    // [2 p + r]: max Frobenius distance between the stored links and the links the kernels apply
+    // for p = 0 FP32 / 1 BF16 storage, r = 0 nine entries / 1 two rows and the rebuilt third
+    unsigned long long round[4];
+};
+hipError_t launch_scan_links(const double2 *U, int V, LinkScan *out, hipStream_t st);
 
 // ---------------------------------------------------------------- projection
 long proj_dot_chunk(long K);
