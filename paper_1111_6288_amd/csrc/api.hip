@@ -490,15 +490,25 @@ ov_ctx::Launch launch_rule(const Geo &g, int n)
     return t;
 }
 
+// Whether a plain launch of n right-hand sides can write the canonical layout (dslash_launch's yc).
+template <class S>
+bool dslash_canonical(const ov_ctx *c, int n)
+{
+    if (c->tune[PrecOf<S>::p][0].chosen) return false;
+    const ov_ctx::Launch t = launch_rule<S>(c->g, n);
+    return t.dir || t.wshare > 1;
+}
+
 template <class S>
 int dslash_launch(ov_ctx *c, const Batch &b, const int *fgroup, const S *x, S *y, double a, bool hw,
                   const S *e1 = nullptr, double c1 = 0, const S *e2 = nullptr, double c2 = 0,
-                  const S *e3 = nullptr, double c3 = 0)
+                  const S *e3 = nullptr, double c3 = 0, double2 *yc = nullptr)
 {
     if (b.n == 0) return OV_OK;
     DsArgs<S> d{};
     d.x = x;
     d.y = y;
+    d.yc = yc;
     d.fstride = (long)field_elems(c);
     d.U = links_of<S>(c);
     d.slots = b.slots;
@@ -996,6 +1006,8 @@ int api_dslash(ov_ctx *c, int op, int nrhs, const std::vector<int> &grp, const v
     const int *fg = dev_ints(c, grp);
     HIPCHK(launch_pack_spinor<S>((const double2 *)x, X, (long)field_elems(c), nullptr, nrhs, c->g.V, c->g.Vp,
                                  c->stream));
+    if (dslash_canonical<S>(c, nrhs))   // the kernel writes y itself
+        return dslash_launch<S>(c, b, fg, X, Y, 1.0, op == OV_OP_HW, nullptr, 0, nullptr, 0, nullptr, 0, (double2 *)y);
     CHK(dslash_launch<S>(c, b, fg, X, Y, 1.0, op == OV_OP_HW));
     HIPCHK(launch_unpack_spinor<S>(Y, (double2 *)y, (long)field_elems(c), nullptr, nrhs, c->g.V, c->g.Vp,
                                    c->stream));
@@ -1025,9 +1037,11 @@ int api_dslash_noalloc(ov_ctx *c, int op, int nrhs, const std::vector<int> &grp,
                                  c->stream));
     const bool prof = c->prof_on;
     c->prof_on = false;
-    const int rc = dslash_launch<S>(c, b, fg, X, Y, 1.0, op == OV_OP_HW);
+    const bool canon = dslash_canonical<S>(c, nrhs);
+    const int rc = dslash_launch<S>(c, b, fg, X, Y, 1.0, op == OV_OP_HW, nullptr, 0, nullptr, 0, nullptr, 0,
+                                    canon ? (double2 *)y : nullptr);
     c->prof_on = prof;
-    CHK(rc);
+    if (rc != OV_OK || canon) return rc;
     HIPCHK(launch_unpack_spinor<S>(Y, (double2 *)y, (long)field_elems(c), nullptr, nrhs, c->g.V, c->g.Vp,
                                    c->stream));
     return OV_OK;

@@ -306,4 +306,17 @@ __device__ __forceinline__ double flip_sign(double v, uint32_t bit)
     return __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, v) ^ ((uint64_t)bit << 32));
 }
 
+// An output component as the storage type holds it, in the canonical layout's
+// complex128.
+template <class S, class R>
+__device__ __forceinline__ double2 stored_value(cx<R> v)
+{
+    if constexpr (sizeof(S) == 4) {
+        const uint32_t w = pack_bf16((float)v.x, (float)v.y);
+        return make_double2((double)bf16_lo(w), (double)bf16_hi(w));
+    } else {
+        return make_double2((double)v.x, (double)v.y);
+    }
+}
+
 }  // namespace ov

@@ -155,13 +155,16 @@ __device__ __forceinline__ cx<R> sum_hops(const cx<R> *__restrict__ g)
     return add_hop<3, +1, SP>(acc, g + 7 * H, c);
 }
 
-template <class S, bool HW, bool EPI, bool REC, bool NT>
+// CAN: the output goes to the canonical layout (12 numbers per site, rows of 13
+// in the LDS of the hops, which have been summed by then) instead of a field.
+template <class S, bool HW, bool EPI, bool REC, bool NT, bool CAN>
 __global__ __launch_bounds__(256, 2) void k_dslash_dir(DsArgs<S> a)
 {
     using R = typename StoreT<S>::real;
     using U = UnitOf<S>;
     using T = typename U::T;
-    __shared__ cx<R> hop[8 * 6 * 64];
+    __shared__ __align__(16) cx<R> hop[8 * 6 * 64];   // at least 24 KiB
+    __shared__ int row_site[64];
     const Geo &g = a.g;
     const int Vp = g.Vp;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = (int)(threadIdx.x & 63);
@@ -208,22 +211,25 @@ __global__ __launch_bounds__(256, 2) void k_dslash_dir(DsArgs<S> a)
     } else {
         dir_hops<3, S, REC>(a, x, s0, tc, g.Lt, g.Lxyz, cmk((R)1, (R)0), out);
     }
+    if (CAN && wave == 0) row_site[lane] = site;
     __syncthreads();
-    if (site >= Vp) return;   // beyond the slab or the lattice
+    if (!CAN && site >= Vp) return;   // beyond the slab or the lattice
 
     const R diag = (R)a.diag, sc = (R)a.a;
     const R cc[3] = {(R)a.c1, (R)a.c2, (R)a.c3};
     const cx<R> *hp = hop + lane;
+    R sg[NMINE];   // gamma5: the second half of the units (taken before the waves part; hipcc 7.2 lost it there)
+#pragma unroll
+    for (int i = 0; i < NMINE; ++i) sg[i] = (HW && q0 + i >= U::N / 2) ? -sc : sc;
     auto finish = [&](auto qc, int i) {
         constexpr int Q = decltype(qc)::value;
-        const R sg = (HW && Q >= U::N / 2) ? -sc : sc;
         cx<R> acc[U::C];
         acc[0] = sum_hops<Q * U::C>(hp);
         if constexpr (U::C == 2) acc[1] = sum_hops<Q * U::C + 1>(hp);
         T v;
 #pragma unroll
         for (int h = 0; h < U::C; ++h) {
-            v.c[h] = cscale(site_term(diag, own[i].c[h], acc[h]), sg);
+            v.c[h] = cscale(site_term(diag, own[i].c[h], acc[h]), sg[i]);
             if constexpr (EPI) {
 #pragma unroll
                 for (int t = 0; t < 3; ++t)
@@ -231,7 +237,8 @@ __global__ __launch_bounds__(256, 2) void k_dslash_dir(DsArgs<S> a)
             }
             if (!real) v.c[h] = cmk((R)0, (R)0);   // padding sites hold zeros in every field
         }
-        st_unit<S, NT>(a.y + off, Vp, Q, (unsigned)site, v);
+        if constexpr (CAN) own[i] = v;
+        else st_unit<S, NT>(a.y + off, Vp, Q, (unsigned)site, v);
     };
 #define OV_UNIT(Q, I) finish(std::integral_constant<int, Q>{}, I)
     if constexpr (U::C == 2) {
@@ -246,14 +253,35 @@ __global__ __launch_bounds__(256, 2) void k_dslash_dir(DsArgs<S> a)
         else { OV_UNIT(9, 0); OV_UNIT(10, 1); OV_UNIT(11, 2); }
     }
 #undef OV_UNIT
+    if constexpr (CAN) {
+        constexpr int ROW = 13;
+        double2 *tr = reinterpret_cast<double2 *>(hop);
+        __syncthreads();   // the hops have been summed
+#pragma unroll
+        for (int i = 0; i < NMINE; ++i)
+            if (i < nmine)
+#pragma unroll
+                for (int h = 0; h < U::C; ++h)
+                    tr[lane * ROW + (q0 + i) * U::C + h] = stored_value<S>(own[i].c[h]);
+        __syncthreads();
+        double2 *yc = a.yc + (long)j * g.V * 12;
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+            const int e = (int)threadIdx.x + 256 * r, row = e / 12, k = e - 12 * row;
+            if (row_site[row] < g.V) yc[(long)row_site[row] * 12 + k] = tr[row * ROW + k];
+        }
+    }
 }
 
 template <class S, bool REC, bool NT>
 static void launch_dir_kernel(const DsArgs<S> &b, bool hw, bool epi, dim3 grid, hipStream_t st)
 {
-    if (epi) hipLaunchKernelGGL((k_dslash_dir<S, true, true, REC, NT>), grid, dim3(256), 0, st, b);
-    else if (hw) hipLaunchKernelGGL((k_dslash_dir<S, true, false, REC, NT>), grid, dim3(256), 0, st, b);
-    else hipLaunchKernelGGL((k_dslash_dir<S, false, false, REC, NT>), grid, dim3(256), 0, st, b);
+    const dim3 blk(256);
+    if (epi) hipLaunchKernelGGL((k_dslash_dir<S, true, true, REC, NT, false>), grid, blk, 0, st, b);
+    else if (b.yc && hw) hipLaunchKernelGGL((k_dslash_dir<S, true, false, REC, NT, true>), grid, blk, 0, st, b);
+    else if (b.yc) hipLaunchKernelGGL((k_dslash_dir<S, false, false, REC, NT, true>), grid, blk, 0, st, b);
+    else if (hw) hipLaunchKernelGGL((k_dslash_dir<S, true, false, REC, NT, false>), grid, blk, 0, st, b);
+    else hipLaunchKernelGGL((k_dslash_dir<S, false, false, REC, NT, false>), grid, blk, 0, st, b);
 }
 
 template <class S>
@@ -269,7 +297,7 @@ hipError_t launch_dslash_dir(const DsArgs<S> &a, bool hw, bool epi, hipStream_t 
     // site block follow each other on its XCD (they share the links in its L2)
     b.xcd_remap = (b.order != 0 || nsb >= 64) ? 1 : 0;
     const int ny = b.order != 0 ? (a.g.V / 8 + 63) / 64 : b.xcd_remap ? (nsb + 7) / 8 : nsb;
-    if (!dslash_dir_fits(a.g) || a.n > (1 << 24)) return hipErrorInvalidValue;
+    if (!dslash_dir_fits(a.g) || a.n > (1 << 24) || (epi && a.yc)) return hipErrorInvalidValue;
     const dim3 grid(b.xcd_remap ? 8 * a.n : a.n, ny);
     if (a.recon) {
         if (a.stream_hint) launch_dir_kernel<S, true, true>(b, hw, epi, grid, st);

@@ -85,7 +85,14 @@ __device__ __forceinline__ void add_shared_hop(const RawSpinor<S> &raw, const LF
 template <class S>
 constexpr int share_depth() { return sizeof(S) == 4 ? 1 : 2; }
 
-template <class S, bool HW, bool EPI, bool REC, bool NT>
+// LDS of a wave for the canonical output: four components of 64 sites, rows of
+// five numbers (20 dwords: 16 lanes of a 16-byte access meet in no bank).
+constexpr int kCanonRow = 5, kCanonWave = 64 * kCanonRow;
+
+// CAN: the output goes to the canonical layout (12 numbers per site), four
+// components at a time through LDS, so that a store covers 16 sites with 64
+// bytes each and the pass that would convert it is not needed.
+template <class S, bool HW, bool EPI, bool REC, bool NT, bool CAN>
 __global__ __launch_bounds__(512, sizeof(S) == 16 ? 2 : 4) void k_dslash_share(DsArgs<S> a)
 {
     using R = typename StoreT<S>::real;
@@ -145,7 +152,7 @@ __global__ __launch_bounds__(512, sizeof(S) == 16 ? 2 : 4) void k_dslash_share(D
         if constexpr (D > 1) fetch(std::integral_constant<int, 1>{});
     }
     __syncthreads();
-    if (!act || site >= g.Vp) return;
+    if (!act || (!CAN && site >= g.Vp)) return;
     const LdsLinks<R, E, REC, SL> lf{lk, lane};
     cx<R> acc[4][3];
 #pragma unroll
@@ -192,7 +199,26 @@ __global__ __launch_bounds__(512, sizeof(S) == 16 ? 2 : 4) void k_dslash_share(D
             if (!real) v[h] = cmk((R)0, (R)0);   // padding sites hold zeros in every field
         }
         S *y = a.y + off;
-        if constexpr (Raw::C == 2) {
+        if constexpr (CAN) {
+            double2 *tr = reinterpret_cast<double2 *>(lds_raw + 8 * E * SL * sizeof(cx<R>)) + wave * kCanonWave;
+#pragma unroll
+            for (int h = 0; h < Raw::C; ++h) tr[lane * kCanonRow + (q * Raw::C + h) % 4] = stored_value<S>(v[h]);
+            if ((q * Raw::C + Raw::C) % 4 == 0) {   // four components are there: the wave writes them
+                const int k0 = q * Raw::C + Raw::C - 4;
+                __builtin_amdgcn_wave_barrier();
+                double2 *yc = a.yc + (long)j * g.V * 12;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int row = 16 * r + (lane >> 2), srow = __shfl(site, row, 64);
+                    const double2 o = tr[row * kCanonRow + (lane & 3)];
+                    if (srow < g.V) {
+                        ov_d2 w = {o.x, o.y};
+                        __builtin_nontemporal_store(w, (ov_d2 *)(yc + (long)srow * 12 + k0 + (lane & 3)));
+                    }
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+        } else if constexpr (Raw::C == 2) {
             if constexpr (NT) stpair_nt<S, R>(y, g.Vp, q, (unsigned)site, v[0], v[1]);
             else stpair<S, R>(y, g.Vp, q, (unsigned)site, v[0], v[1]);
         } else {
@@ -202,21 +228,26 @@ __global__ __launch_bounds__(512, sizeof(S) == 16 ? 2 : 4) void k_dslash_share(D
     }
 }
 
-template <class S, bool REC, bool NT>
-static hipError_t launch_share_kernel(const DsArgs<S> &b, bool hw, bool epi, dim3 grid, size_t lds, hipStream_t st)
+template <class S, bool HW, bool EPI, bool REC, bool NT, bool CAN>
+static hipError_t launch_share_kernel(const DsArgs<S> &b, dim3 grid, size_t lds, hipStream_t st)
 {
-    const void *fn = epi  ? (const void *)k_dslash_share<S, true, true, REC, NT>
-                     : hw ? (const void *)k_dslash_share<S, true, false, REC, NT>
-                          : (const void *)k_dslash_share<S, false, false, REC, NT>;
-    if (lds > 64 * 1024) {   // staged full FP64 links exceed the default limit of dynamic LDS
-        const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (lds > 64 * 1024) {   // more than the default limit of dynamic LDS
+        const hipError_t e = hipFuncSetAttribute((const void *)k_dslash_share<S, HW, EPI, REC, NT, CAN>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if (e != hipSuccess) return e;
     }
-    const dim3 blk(64 * b.wshare);
-    if (epi) hipLaunchKernelGGL((k_dslash_share<S, true, true, REC, NT>), grid, blk, lds, st, b);
-    else if (hw) hipLaunchKernelGGL((k_dslash_share<S, true, false, REC, NT>), grid, blk, lds, st, b);
-    else hipLaunchKernelGGL((k_dslash_share<S, false, false, REC, NT>), grid, blk, lds, st, b);
+    hipLaunchKernelGGL((k_dslash_share<S, HW, EPI, REC, NT, CAN>), grid, dim3(64 * b.wshare), lds, st, b);
     return hipGetLastError();
+}
+
+template <class S, bool REC, bool NT>
+static hipError_t launch_share_mode(const DsArgs<S> &b, bool hw, bool epi, dim3 grid, size_t lds, hipStream_t st)
+{
+    if (epi) return launch_share_kernel<S, true, true, REC, NT, false>(b, grid, lds, st);
+    if (b.yc) return hw ? launch_share_kernel<S, true, false, REC, NT, true>(b, grid, lds, st)
+                        : launch_share_kernel<S, false, false, REC, NT, true>(b, grid, lds, st);
+    return hw ? launch_share_kernel<S, true, false, REC, NT, false>(b, grid, lds, st)
+              : launch_share_kernel<S, false, false, REC, NT, false>(b, grid, lds, st);
 }
 
 template <class S>
@@ -224,19 +255,19 @@ hipError_t launch_dslash_share(const DsArgs<S> &a, bool hw, bool epi, hipStream_
 {
     using R = typename StoreT<S>::real;
     if (a.n <= 0) return hipSuccess;
-    if (a.wshare < 2 || a.wshare > 8) return hipErrorInvalidValue;
+    if (a.wshare < 2 || a.wshare > 8 || (epi && a.yc)) return hipErrorInvalidValue;
     DsArgs<S> b = a;
     int nbx = site_blocks(b, 64);
     const int E = a.recon ? lds_link_components<R, true>() : lds_link_components<R, false>();
-    const size_t need = (size_t)8 * E * 64 * sizeof(cx<R>);
+    const size_t need = (size_t)8 * E * 64 * sizeof(cx<R>) + (a.yc ? (size_t)a.wshare * kCanonWave * sizeof(double2) : 0);
     const size_t cap = a.blocks_per_cu > 0 ? (size_t)(160 * 1024) / (size_t)a.blocks_per_cu - 256 : 0;
     const size_t lds = need > cap ? need : cap;
     const dim3 grid(nbx, (a.n + a.wshare - 1) / a.wshare);
     if (a.recon)
-        return a.stream_hint ? launch_share_kernel<S, true, true>(b, hw, epi, grid, lds, st)
-                             : launch_share_kernel<S, true, false>(b, hw, epi, grid, lds, st);
-    return a.stream_hint ? launch_share_kernel<S, false, true>(b, hw, epi, grid, lds, st)
-                         : launch_share_kernel<S, false, false>(b, hw, epi, grid, lds, st);
+        return a.stream_hint ? launch_share_mode<S, true, true>(b, hw, epi, grid, lds, st)
+                             : launch_share_mode<S, true, false>(b, hw, epi, grid, lds, st);
+    return a.stream_hint ? launch_share_mode<S, false, true>(b, hw, epi, grid, lds, st)
+                         : launch_share_mode<S, false, false>(b, hw, epi, grid, lds, st);
 }
 
 template hipError_t launch_dslash_share<double2>(const DsArgs<double2> &, bool, bool, hipStream_t);

@@ -14,6 +14,8 @@ template <class S>
 struct DsArgs {
     const S *x;              // input batch (planes), read at the 8 neighbours and the own site
     S *y;                    // output batch, must not alias x
+    double2 *yc;             // canonical complex128 [n][V][4][3] to write instead of y (launch_dslash_dir and
+                             // launch_dslash_share without an epilogue), or NULL
     long fstride;            // storage elements between consecutive fields
     const S *U;              // links [4][9][Vp]
     const int *slots;        // storage index of batch entry j (NULL: j)
