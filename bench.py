@@ -82,7 +82,7 @@ def parse():
 
 def kernel_source_hash():
     h = hashlib.sha256()
-    for f in ("dslash_site.h", "dslash_device.h", "spin.h", "ov_device.h", "ov_internal.h"):
+    for f in ("dslash_site.h", "dslash_share.hip", "dslash_device.h", "spin.h", "ov_device.h", "ov_internal.h"):
         h.update(open(os.path.join(ROOT, "paper_1111_6288_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]
 

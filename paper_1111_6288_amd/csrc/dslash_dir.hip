@@ -18,8 +18,10 @@
 // in turn.  It also has four times the wavefronts for the same sites.
 // Mean of a plain and a fused launch in a captured graph (an empty node takes
 // 1.6 us), site-parallel kernel and this one:
-//   FP64 12 RHS of 4^4 16.7 -> 5.1 us, FP32 4 RHS of 8^3x16 16.3 -> 6.7 us,
-//   FP64 1 RHS of 16^3x32 37.7 -> 31 us, of 24^3x48 222 -> 175 us.
+//   FP64 12 RHS of 4^4 16.7 -> 5.1 us, FP32 4 RHS of 8^3x16 16.3 -> 6.6 us,
+//   FP64 1 RHS of 16^3x32 37.7 -> 28 us, of 24^3x48 222 -> 157 us.
+// Loading every argument at once at the top instead of where it is needed, and slots and field
+// groups as arguments instead of lists, gained nothing (1.00x; the latter 0.94x on 4^4).
 #include <type_traits>
 
 #include "dslash_device.h"
