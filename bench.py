@@ -534,7 +534,7 @@ def main():
                 "traffic": traffic, "traffic_bytes_per_launch": traffic_bytes,
                 "kernel": ("k_dslash_tm<float2,HW,EPI,W,REC> (t-marching dslash + fused Clenshaw epilogue)"
                            if tuned["clenshaw"]["site_order"] == 2
-                           else "k_dslash_lds<float2,NR,Q,HW,EPI,REC> (dslash with LDS-shared links + fused "
+                           else "k_dslash_share<float2,HW,EPI,REC,NT> (dslash with LDS-shared links + fused "
                                 "Clenshaw epilogue)" if tuned["clenshaw"].get("wshare", 1) > 1
                            else "k_dslash<float2,NR,Q,HW,EPI,REC> (dslash + fused Clenshaw epilogue)"),
                 "two_row_links": two_row,
