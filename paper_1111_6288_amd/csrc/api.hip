@@ -441,9 +441,10 @@ const uint32_t *links_of<uint32_t>(const ov_ctx *c) { return c->U16; }
 // (an empty node takes 1.6 us).
 //
 // Direction waves for small batches, which wait for memory latency, not bandwidth: FP64 12 RHS of
-// 4^4 16.7 (two RHS per thread) -> 5.1 us, FP32 4 RHS of 8^3x16 16.3 -> 6.6 us.  Every right-hand
+// 4^4 16.7 (two RHS per thread) -> 4.7 us, FP32 4 RHS of 8^3x16 16.3 -> 6.1 us.  Every right-hand
 // side reads all eight links and rebuilds their third rows, so sharing staged links wins once the
-// fields outgrow the caches or, in FP64, the batch is long.  Direction waves / shared links:
+// fields outgrow the caches or, in FP64, the batch is long.  Direction waves (four
+// per block; eight, which such batches get, take up to 8 % less, 0.3 % at 12 RHS of 12^3x24) / shared links:
 //   FP64 6x5x7x10 12 RHS (5 MB) 8.7 / 12.2 us, 12^3x24 6 RHS (48 MB) 43.7 / 46.0, 8 RHS 58.8 / 59.8, 12 RHS (96 MB) 94 / 88,
 //        8^3x16 8 RHS 14.3 / 14.1, 24 RHS (38 MB) 35.7 / 33.0, 16^3x32 2 RHS 49 / 49, 4 RHS 102 / 95;
 //   FP32 12^3x24 8 RHS (32 MB) 28.3 / 29.6, 12 RHS (48 MB) 41.1 / 40.2, 16^3x32 6 RHS (75 MB) 77 / 69;

@@ -1,13 +1,13 @@
-// H_w / D_w for small batches: one wave per direction of the stencil.
+// H_w / D_w for small batches: one wave per hop or per direction of the stencil.
 //
 // Same operator and epilogue as the site-parallel kernels:
 //   y_r = a * G (D_w x_r)  +  c1 e1_r + c2 e2_r + c3 e3_r          (own site)
 //
-// The four waves of a workgroup cover the same 64 sites of one right-hand
-// side; wave mu gathers the two hops of direction mu and leaves the link times
-// half spinor of each in LDS ([hop][2 x 3 components][lane]), after which wave
-// w sums a quarter of the components, hop by hop in the order of the
-// site-parallel kernels, so the result has the same bits as theirs.
+// The eight (or four) waves of a workgroup cover the same 64 sites of one
+// right-hand side; each gathers one hop (or both hops of a direction) and
+// leaves the link times half spinor in LDS ([hop][2 x 3 components][lane]),
+// after which each sums a share of the components, hop by hop in the order of
+// the site-parallel kernels, so the result has the same bits as theirs.
 //
 // What bounds a small batch is memory latency.  The loads of a thread (two
 // links, two neighbours, its share of the own-site operands) depend on nothing
@@ -15,11 +15,11 @@
 // them, so they are all in flight together: the kernel waits for memory about
 // once, where a thread that walks the eight hops one after the other, each
 // behind its boundary branch, waits for the links and the spinor of every hop
-// in turn.  It also has four times the wavefronts for the same sites.
+// in turn.  It also has eight times the wavefronts for the same sites.
 // Mean of a plain and a fused launch in a captured graph (an empty node takes
 // 1.6 us), site-parallel kernel and this one:
-//   FP64 12 RHS of 4^4 16.7 -> 5.1 us, FP32 4 RHS of 8^3x16 16.3 -> 6.6 us,
-//   FP64 1 RHS of 16^3x32 37.7 -> 28 us, of 24^3x48 222 -> 157 us.
+//   FP64 12 RHS of 4^4 16.7 -> 4.7 us, FP32 4 RHS of 8^3x16 16.3 -> 6.1 us,
+//   FP64 1 RHS of 16^3x32 37.7 -> 27 us, of 24^3x48 222 -> 157 us.
 // Loading every argument at once at the top instead of where it is needed, and slots and field
 // groups as arguments instead of lists, gained nothing (1.00x; the latter 0.94x on 4^4).
 #include <type_traits>
@@ -67,10 +67,10 @@ __device__ __forceinline__ void st_unit(S *__restrict__ f, int Vp, int q, unsign
     }
 }
 
-// Both hops of direction MU at `site` (a real site): link times half spinor
-// to out[6 components at stride 64], the forward hop first, the backward hop
-// 6 x 64 behind.
-template <int MU, class S, bool REC>
+// Hops of direction MU at `site` (a real site), HOPS = 1 forward, 2 backward, 3
+// both: link times half spinor to out[6 components at stride 64], the forward
+// hop first, the backward hop 6 x 64 behind.
+template <int MU, int HOPS, class S, bool REC>
 __device__ __forceinline__ void dir_hops(const DsArgs<S> &a, const S *__restrict__ x, int site, int cmu, int Lmu,
                                          int stride, cx<typename StoreT<S>::real> ph,
                                          cx<typename StoreT<S>::real> *__restrict__ out)
@@ -84,22 +84,26 @@ __device__ __forceinline__ void dir_hops(const DsArgs<S> &a, const S *__restrict
     const unsigned eu = (unsigned)(wb ? site + (Lmu - 1) * stride : site - stride) * (unsigned)Raw::B;
     cx<R> uf[3][3], ub[3][3], pf[4][3], pb[4][3];
     Raw rf, rb;
-    rf.load(x, Vp, neighbour_offset<S>(site, wf, Lmu, stride, bc));
-    rb.load(x, Vp, neighbour_offset<S>(site, wb, Lmu, -stride, bc));
-    load_link_buf<S, REC>(a.U, MU, Vp, es, uf);
-    load_link_buf<S, REC>(a.U, MU, Vp, eu, ub);
-    rf.spinor(pf);
-    rb.spinor(pb);
+    if constexpr (HOPS & 1) rf.load(x, Vp, neighbour_offset<S>(site, wf, Lmu, stride, bc));
+    if constexpr (HOPS & 2) rb.load(x, Vp, neighbour_offset<S>(site, wb, Lmu, -stride, bc));
+    if constexpr (HOPS & 1) load_link_buf<S, REC>(a.U, MU, Vp, es, uf);
+    if constexpr (HOPS & 2) load_link_buf<S, REC>(a.U, MU, Vp, eu, ub);
     cx<R> hf[2][3], hb[2][3];
-    project<MU, -1>(pf, hf);
-    project<MU, +1>(pb, hb);
+    if constexpr (HOPS & 1) {
+        rf.spinor(pf);
+        project<MU, -1>(pf, hf);
+    }
+    if constexpr (HOPS & 2) {
+        rb.spinor(pb);
+        project<MU, +1>(pb, hb);
+    }
     if (MU == 0) {
 #pragma unroll
         for (int k = 0; k < 2; ++k)
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                hf[k][c] = phase_mul<S>(ph, hf[k][c], k, c, a.n == 1);
-                hb[k][c] = phase_mul<S>(cmk(ph.x, -ph.y), hb[k][c], k, c, a.n == 1);
+                if constexpr (HOPS & 1) hf[k][c] = phase_mul<S>(ph, hf[k][c], k, c, a.n == 1);
+                if constexpr (HOPS & 2) hb[k][c] = phase_mul<S>(cmk(ph.x, -ph.y), hb[k][c], k, c, a.n == 1);
             }
     }
     if (bc < 0.0f) {   // antiperiodic
@@ -108,22 +112,26 @@ __device__ __forceinline__ void dir_hops(const DsArgs<S> &a, const S *__restrict
         for (int k = 0; k < 2; ++k)
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                hf[k][c] = cmk(flip_sign(hf[k][c].x, ff), flip_sign(hf[k][c].y, ff));
-                hb[k][c] = cmk(flip_sign(hb[k][c].x, fb), flip_sign(hb[k][c].y, fb));
+                if constexpr (HOPS & 1) hf[k][c] = cmk(flip_sign(hf[k][c].x, ff), flip_sign(hf[k][c].y, ff));
+                if constexpr (HOPS & 2) hb[k][c] = cmk(flip_sign(hb[k][c].x, fb), flip_sign(hb[k][c].y, fb));
             }
     }
 #pragma unroll
     for (int k = 0; k < 2; ++k)
 #pragma unroll
         for (int aa = 0; aa < 3; ++aa) {
-            cx<R> t = REC && aa == 2 ? cmul_i(uf[aa][0], hf[k][0]) : cmul(uf[aa][0], hf[k][0]);
-            cfma(t, uf[aa][1], hf[k][1]);
-            cfma(t, uf[aa][2], hf[k][2]);
-            out[(k * 3 + aa) * 64] = t;
-            cx<R> w = MU == 0 ? cmulc(ub[0][aa], hb[k][0]) : cmulc_r(ub[0][aa], hb[k][0]);
-            cfmac(w, ub[1][aa], hb[k][1]);
-            cfmac(w, ub[2][aa], hb[k][2]);
-            out[(6 + k * 3 + aa) * 64] = w;
+            if constexpr (HOPS & 1) {
+                cx<R> t = REC && aa == 2 ? cmul_i(uf[aa][0], hf[k][0]) : cmul(uf[aa][0], hf[k][0]);
+                cfma(t, uf[aa][1], hf[k][1]);
+                cfma(t, uf[aa][2], hf[k][2]);
+                out[(k * 3 + aa) * 64] = t;
+            }
+            if constexpr (HOPS & 2) {
+                cx<R> w = MU == 0 ? cmulc(ub[0][aa], hb[k][0]) : cmulc_r(ub[0][aa], hb[k][0]);
+                cfmac(w, ub[1][aa], hb[k][1]);
+                cfmac(w, ub[2][aa], hb[k][2]);
+                out[(6 + k * 3 + aa) * 64] = w;
+            }
         }
 }
 
@@ -159,9 +167,22 @@ __device__ __forceinline__ cx<R> sum_hops(const cx<R> *__restrict__ g)
 
 // CAN: the output goes to the canonical layout (12 numbers per site, rows of 13
 // in the LDS of the hops, which have been summed by then) instead of a field.
+//
+// Eight waves, one hop each, have half the loads and arithmetic of a hop pair
+// in a row; four waves are fewer to start and to meet at the barrier.  Mean of
+// a plain and a fused launch, four / eight waves:
+//   FP64 12 RHS of 4^4 5.0 / 4.7 us, FP32 5 RHS of 6x5x7x10 4.8 / 4.4, FP32 4 RHS of 8^3x16 6.5 / 6.1,
+//   FP64 4 RHS of 8^3x16 8.7 / 8.2, of 12^3x24 32.1 / 29.4, FP64 1 RHS of 16^3x32 28.9 / 27.3,
+// but in batches that stream past the caches four read less again:
+//   FP64 1 RHS of 24^3x48 159 / 163, 2 RHS 294 / 307, FP32 2 RHS 139 / 141,
+// and a single call with canonical output is 10.2 / 10.4 us on 8^3x16.
+constexpr int dir_waves(bool NT, bool CAN) { return NT || CAN ? 4 : 8; }
+
 template <class S, bool HW, bool EPI, bool REC, bool NT, bool CAN>
-__global__ __launch_bounds__(256, 2) void k_dslash_dir(DsArgs<S> a)
+__global__ __launch_bounds__(dir_waves(NT, CAN) * 64, dir_waves(NT, CAN) == 8 && !(sizeof(S) == 16 && !REC) ? 4 : 2)
+void k_dslash_dir(DsArgs<S> a)
 {
+    constexpr bool W8 = dir_waves(NT, CAN) == 8;
     using R = typename StoreT<S>::real;
     using U = UnitOf<S>;
     using T = typename U::T;
@@ -184,11 +205,13 @@ __global__ __launch_bounds__(256, 2) void k_dslash_dir(DsArgs<S> a)
     const int s0 = real ? site : 0;   // other lanes load site 0 and drop the result
     int xc, yc, zc, tc;
     site_coords(g, s0, xc, yc, zc, tc);
-    // units this wave writes, from q0 on: three of twelve, or of six one for waves 0 and 1 (wave 0
-    // has the background phase to apply) and two for waves 2 and 3
-    constexpr int NMINE = U::C == 2 ? 2 : 3;
-    const int q0 = U::C == 2 ? (wave < 2 ? wave : 2 * wave - 2) : 3 * wave;
-    const int nmine = U::C == 2 ? (wave < 2 ? 1 : 2) : 3;
+    // units this wave writes, from q0 on: of four waves three of twelve, or of six one for waves 0 and 1
+    // (wave 0 has the background phase to apply) and two for waves 2 and 3
+    // Of eight waves, 2 to 7 write one of six, or 0 to 3 one and 4 to 7 two of twelve.
+    constexpr int NMINE = W8 ? (U::C == 2 ? 1 : 2) : U::C == 2 ? 2 : 3;
+    const int q0 = W8 ? (U::C == 2 ? (wave < 2 ? 0 : wave - 2) : wave < 4 ? wave : 2 * wave - 4)
+                      : U::C == 2 ? (wave < 2 ? wave : 2 * wave - 2) : 3 * wave;
+    const int nmine = W8 ? (U::C == 2 ? (wave < 2 ? 0 : 1) : wave < 4 ? 1 : 2) : U::C == 2 ? (wave < 2 ? 1 : 2) : 3;
     T own[NMINE], ep[3][NMINE];
     const S *e[3] = {a.e1, a.e2, a.e3};
 #pragma unroll
@@ -201,18 +224,25 @@ __global__ __launch_bounds__(256, 2) void k_dslash_dir(DsArgs<S> a)
                 if (e[t]) ep[t][i] = ld_unit<S, NT>(e[t] + off, Vp, q, (unsigned)s0 * (unsigned)RawSpinor<S>::B);
         }
     }
-    cx<R> *out = hop + wave * 12 * 64 + lane;
-    if (wave == 0) {
+    // of eight waves the even ones take the forward hops (0 and 1 have the background phase)
+    const int mu = W8 ? wave >> 1 : wave;
+    cx<R> *out = hop + mu * 12 * 64 + lane;
+    cx<R> ph = cmk((R)1, (R)0);
+    if (mu == 0) {
         const int grp = a.fgroup ? a.fgroup[s] : 0;
         const cx<double> pd = a.phase[grp * g.Lt + tc];
-        dir_hops<0, S, REC>(a, x, s0, xc, g.Lx, 1, cmk((R)pd.x, (R)pd.y), out);
-    } else if (wave == 1) {
-        dir_hops<1, S, REC>(a, x, s0, yc, g.Ly, g.Lx, cmk((R)1, (R)0), out);
-    } else if (wave == 2) {
-        dir_hops<2, S, REC>(a, x, s0, zc, g.Lz, g.Lxy, cmk((R)1, (R)0), out);
-    } else {
-        dir_hops<3, S, REC>(a, x, s0, tc, g.Lt, g.Lxyz, cmk((R)1, (R)0), out);
+        ph = cmk((R)pd.x, (R)pd.y);
     }
+    auto hops = [&](auto h) {
+        constexpr int H = decltype(h)::value;
+        if (mu == 0) dir_hops<0, H, S, REC>(a, x, s0, xc, g.Lx, 1, ph, out);
+        else if (mu == 1) dir_hops<1, H, S, REC>(a, x, s0, yc, g.Ly, g.Lx, ph, out);
+        else if (mu == 2) dir_hops<2, H, S, REC>(a, x, s0, zc, g.Lz, g.Lxy, ph, out);
+        else dir_hops<3, H, S, REC>(a, x, s0, tc, g.Lt, g.Lxyz, ph, out);
+    };
+    if constexpr (!W8) hops(std::integral_constant<int, 3>{});
+    else if (wave & 1) hops(std::integral_constant<int, 2>{});
+    else hops(std::integral_constant<int, 1>{});
     if (CAN && wave == 0) row_site[lane] = site;
     __syncthreads();
     if (!CAN && site >= Vp) return;   // beyond the slab or the lattice
@@ -243,7 +273,23 @@ __global__ __launch_bounds__(256, 2) void k_dslash_dir(DsArgs<S> a)
         else st_unit<S, NT>(a.y + off, Vp, Q, (unsigned)site, v);
     };
 #define OV_UNIT(Q, I) finish(std::integral_constant<int, Q>{}, I)
-    if constexpr (U::C == 2) {
+    if constexpr (W8 && U::C == 2) {
+        if (wave == 2) { OV_UNIT(0, 0); }
+        else if (wave == 3) { OV_UNIT(1, 0); }
+        else if (wave == 4) { OV_UNIT(2, 0); }
+        else if (wave == 5) { OV_UNIT(3, 0); }
+        else if (wave == 6) { OV_UNIT(4, 0); }
+        else if (wave == 7) { OV_UNIT(5, 0); }
+    } else if constexpr (W8) {
+        if (wave == 0) { OV_UNIT(0, 0); }
+        else if (wave == 1) { OV_UNIT(1, 0); }
+        else if (wave == 2) { OV_UNIT(2, 0); }
+        else if (wave == 3) { OV_UNIT(3, 0); }
+        else if (wave == 4) { OV_UNIT(4, 0); OV_UNIT(5, 1); }
+        else if (wave == 5) { OV_UNIT(6, 0); OV_UNIT(7, 1); }
+        else if (wave == 6) { OV_UNIT(8, 0); OV_UNIT(9, 1); }
+        else { OV_UNIT(10, 0); OV_UNIT(11, 1); }
+    } else if constexpr (U::C == 2) {
         if (wave == 0) { OV_UNIT(0, 0); }
         else if (wave == 1) { OV_UNIT(1, 0); }
         else if (wave == 2) { OV_UNIT(2, 0); OV_UNIT(3, 1); }
@@ -278,7 +324,7 @@ __global__ __launch_bounds__(256, 2) void k_dslash_dir(DsArgs<S> a)
 template <class S, bool REC, bool NT>
 static void launch_dir_kernel(const DsArgs<S> &b, bool hw, bool epi, dim3 grid, hipStream_t st)
 {
-    const dim3 blk(256);
+    const dim3 blk(64 * dir_waves(NT, b.yc != nullptr));
     if (epi) hipLaunchKernelGGL((k_dslash_dir<S, true, true, REC, NT, false>), grid, blk, 0, st, b);
     else if (b.yc && hw) hipLaunchKernelGGL((k_dslash_dir<S, true, false, REC, NT, true>), grid, blk, 0, st, b);
     else if (b.yc) hipLaunchKernelGGL((k_dslash_dir<S, false, false, REC, NT, true>), grid, blk, 0, st, b);
