@@ -11,8 +11,8 @@
 // vectors on 24^3x48: 3.4 GB at 5.9 TB/s, 1.8 GB of it neighbours read again),
 // BF16 the vector arithmetic.  So loads take their addresses from scalar
 // resources, boundaries cost no branch (the staged link holds the sign of an
-// antiperiodic hop, a Dirichlet neighbour is fetched from beyond the plane,
-// which reads as zero), and with straight code the next neighbours are
+// antiperiodic hop or zeros across a Dirichlet boundary, whose neighbour is
+// fetched from beyond the plane, which reads as zero), and with straight code the next neighbours are
 // requested while one is worked on.  Mean of a plain and a fused launch of 12
 // vectors against the kernel with a branch per hop and 64-bit lane addresses:
 //   16^3x32  FP64 304 -> 281 us, FP32 145 -> 133, BF16 97 -> 103 (5: 48 -> 41)
@@ -111,13 +111,17 @@ __global__ __launch_bounds__(512, sizeof(S) == 16 ? 2 : 4) void k_dslash_share(D
     for (int slot = wave; slot < 8; slot += W) {
         cx<R> *dst = lk + slot * E * SL + lane;
         stage_link<S, R, REC, E, SL>(a, slot, s0, xc, yc, zc, tc, dst);
-        if constexpr (E == 9) {   // antiperiodic hops: the link carries the sign
-            const int mu = slot & 3;
-            const int c = mu == 0 ? xc : mu == 1 ? yc : mu == 2 ? zc : tc;
-            const int L = mu == 0 ? g.Lx : mu == 1 ? g.Ly : mu == 2 ? g.Lz : g.Lt;
-            if (g.bcf[mu] < 0 && c == (slot < 4 ? L - 1 : 0))
+        const int mu = slot & 3;
+        const int c = mu == 0 ? xc : mu == 1 ? yc : mu == 2 ? zc : tc;
+        const int L = mu == 0 ? g.Lx : mu == 1 ? g.Ly : mu == 2 ? g.Lz : g.Lt;
+        if (g.bcf[mu] <= 0 && c == (slot < 4 ? L - 1 : 0)) {
+            if (g.bcf[mu] == 0) {   // Dirichlet: the hop is dropped, whatever its link holds
+#pragma unroll
+                for (int k = 0; k < E; ++k) dst[k * SL] = cmk((R)0, (R)0);
+            } else if constexpr (E == 9) {   // antiperiodic hops: the link carries the sign
 #pragma unroll
                 for (int k = 0; k < 9; ++k) dst[k * SL] = cmk(-dst[k * SL].x, -dst[k * SL].y);
+            }
         }
     }
 
