@@ -89,6 +89,16 @@ constexpr int share_depth() { return sizeof(S) == 4 ? 1 : 2; }
 // five numbers (20 dwords: 16 lanes of a 16-byte access meet in no bank).
 constexpr int kCanonRow = 5, kCanonWave = 64 * kCanonRow;
 
+// Orders the LDS accesses of a wave's lanes before and after it.  The hardware
+// keeps them in order; the fences hold the compiler to it, which the barrier
+// alone does not (no instruction comes of either).
+__device__ __forceinline__ void wave_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // CAN: the output goes to the canonical layout (12 numbers per site), four
 // components at a time through LDS, so that a store covers 16 sites with 64
 // bytes each and the pass that would convert it is not needed.
@@ -209,7 +219,7 @@ __global__ __launch_bounds__(512, sizeof(S) == 16 ? 2 : 4) void k_dslash_share(D
             for (int h = 0; h < Raw::C; ++h) tr[lane * kCanonRow + (q * Raw::C + h) % 4] = stored_value<S>(v[h]);
             if ((q * Raw::C + Raw::C) % 4 == 0) {   // four components are there: the wave writes them
                 const int k0 = q * Raw::C + Raw::C - 4;
-                __builtin_amdgcn_wave_barrier();
+                wave_lds_sync();
                 double2 *yc = a.yc + (long)j * g.V * 12;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
@@ -220,7 +230,7 @@ __global__ __launch_bounds__(512, sizeof(S) == 16 ? 2 : 4) void k_dslash_share(D
                         __builtin_nontemporal_store(w, (ov_d2 *)(yc + (long)srow * 12 + k0 + (lane & 3)));
                     }
                 }
-                __builtin_amdgcn_wave_barrier();
+                wave_lds_sync();   // read before the next four take their place
             }
         } else if constexpr (Raw::C == 2) {
             if constexpr (NT) stpair_nt<S, R>(y, g.Vp, q, (unsigned)site, v[0], v[1]);
