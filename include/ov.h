@@ -444,9 +444,17 @@ int ov_dense_heev(int n, const double *A, double *w, double *Z);
  *   gx_dev   [V][4][3] complex128, dL/dRe x + i dL/dIm x = s g.
  * The forward Clenshaw vectors are checkpointed every ckpt_every terms
  * (>= 1) and replayed segment by segment.  FP64 throughout.  Synchronises.
+ *
+ * Device memory: K + 2 ceil(n / K) + 19 FP64 fields and a few small arrays,
+ * with K = min(ckpt_every, n).  K more fields save n of the H_w launches of
+ * gU and geta; they are taken where they are at most `bytes` of
+ * ov_set_adjoint_memory (default 8 GiB; 0: never; OV_EINVAL below 0) and the
+ * whole fits half of the free memory.  Like the rest of the workspace they
+ * stay with the context.  The results are the same bits either way.
  */
 int ov_sign_backward(ov_ctx *ctx, int field, const void *x_dev, const void *g_dev,
                      void *gU_dev, double *geta, void *gx_dev, int ckpt_every);
+int ov_set_adjoint_memory(ov_ctx *ctx, int64_t bytes);
 
 /*
  * Per-kernel timing with HIP events recorded on the context's stream around

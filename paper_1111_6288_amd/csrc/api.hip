@@ -143,6 +143,7 @@ struct ov_ctx {
     void *scratch = nullptr;
 
     size_t mem_bytes = 0;
+    size_t adjoint_mem = 8ul << 30;   // most that ov_sign_backward may add to save launches
 
     // captured pipelines (hipGraph), keyed by everything the launch sequence depends on
     bool use_graphs = true;
@@ -1954,13 +1955,17 @@ int api_backward(ov_ctx *c, int f, const void *x_dev, const void *g_dev, void *g
     const size_t fb = align_up(field_bytes<S>(c));
     const size_t need = (11 + (size_t)K + 2 * nseg) * fb + align_up(36ul * c->g.Vp * 16) + align_up(8ul * nb_fin) +
                         sign_bufs_bytes<S>(c, 1);
-    // K more hold H_w b_{k+1} of a replayed segment, which the sweep needs again (n launches fewer):
-    // taken where the arena has them already or half of the free memory does
+    // K more hold H_w b_{k+1} of a replayed segment, which the sweep needs again (n launches fewer).  The
+    // arena stays grown, so they are bounded (ov_set_adjoint_memory), and taken only where it has them
+    // already or half of the free memory does.
     const size_t more = (size_t)K * fb;
-    bool keep_h = need + more <= c->ws_size;
-    if (!keep_h) {
+    bool keep_h = (gU_dev || geta) && more <= c->adjoint_mem;
+    if (keep_h && need + more > c->ws_size) {
         size_t avail = 0, total = 0;
-        if (hipMemGetInfo(&avail, &total) != hipSuccess) avail = 0;
+        if (hipMemGetInfo(&avail, &total) != hipSuccess) {
+            (void)hipGetLastError();   // not the next launch's error
+            avail = 0;
+        }
         keep_h = need + more <= (avail + c->ws_size) / 2;
     }
     int rc = ws_reserve(c, need + (keep_h ? more : 0));
@@ -2249,6 +2254,14 @@ int ov_sign_backward(ov_ctx *c, int field, const void *x_dev, const void *g_dev,
     CHK(clear_norm_flag(c));
     return with_norm_status(c, api_backward(c, field, x_dev, g_dev, gU_dev, geta, gx_dev,
                                             std::min(ckpt_every, c->npoly)));
+}
+
+int ov_set_adjoint_memory(ov_ctx *c, int64_t bytes)
+{
+    CHK(check_ctx(c));
+    if (bytes < 0) return fail(c, OV_EINVAL, "bytes must be >= 0");
+    c->adjoint_mem = (size_t)bytes;
+    return OV_OK;
 }
 
 int ov_autotune(ov_ctx *c, int prec, int nrhs, const char *cache_path)

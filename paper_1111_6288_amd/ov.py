@@ -90,6 +90,7 @@ def _load():
         "ov_dov_apply": ([vp, i, i, cp(i), cp(d), i, vp, vp], i),
         "ov_deflated_cg": ([vp, i, cp(i), cp(d), vp, vp, cp(CgOpts), cp(CgReport)], i),
         "ov_sign_backward": ([vp, i, vp, vp, vp, cp(d), vp, i], i),
+        "ov_set_adjoint_memory": ([vp, C.c_int64], i),
         "ov_hw_eigensolve": ([vp, i, cp(EigOpts), vp, vp, cp(d), cp(d), i, cp(EigReport)], i),
         "ov_dense_heev": ([i, cp(d), cp(d), cp(d)], i),
         "ov_multishift_cg": ([vp, i, cp(i), i, cp(d), vp, vp, cp(MscgOpts), cp(MscgReport), cp(d)], i),
@@ -131,7 +132,7 @@ EXPORTED = ("ov_create", "ov_destroy", "ov_set_stream", "ov_last_error", "ov_upl
             "ov_set_launch_config", "ov_hw_eigensolve", "ov_dense_heev", "ov_multishift_cg",
             "ov_dov_eigensolve", "ov_timeslice_norm2", "ov_correlator_deta", "ov_set_link_reconstruct",
             "ov_get_link_format", "ov_dslash_noalloc", "ov_set_norm_check", "ov_norm_status", "ov_get_sign_norm",
-            "ov_pion_correlator", "ov_ratio_R")
+            "ov_pion_correlator", "ov_ratio_R", "ov_set_adjoint_memory")
 
 
 def _ints(v):
@@ -331,6 +332,10 @@ class Context:
                                        C.byref(ge) if want_eta else None,
                                        _dev(gx, (self.V, 4, 3), "gx") if want_x else None, int(ckpt_every)))
         return gU, (ge.value if want_eta else None), gx
+
+    def set_adjoint_memory(self, nbytes):
+        """Most device memory that sign_backward adds to its workspace to save launches (0: none)."""
+        return self._chk(lib.ov_set_adjoint_memory(self._h, int(nbytes)))
 
     def multishift_cg(self, b, masses, fields=None, tol=1e-10, maxiter=5000, adaptive=True, min_order=20,
                       refine=True, inner_prec="fp64", raise_on_noconv=True):
