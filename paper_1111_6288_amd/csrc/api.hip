@@ -2062,7 +2062,7 @@ int api_backward(ov_ctx *c, int f, const void *x_dev, const void *g_dev, void *g
     CHK(dslash_launch<S>(c, b, fg, wbar, zbar, invN, true));
 
     HIPCHK(hipMemsetAsync(G, 0, 36ul * c->g.Vp * 16, c->stream));
-    // terms Re<u, dQ v> are collected and added to G together
+    // terms Re<u, dQ v>, added to G in pairs: a pair as soon as it is complete (its vectors are overwritten next)
     ForceArgs fa{};
     fa.G = G;
     fa.g = c->g;
@@ -2125,7 +2125,6 @@ int api_backward(ov_ctx *c, int f, const void *x_dev, const void *g_dev, void *g
                 CHK(force(zbar, t2, kap * invN * invN));
                 CHK(dslash_launch<S>(c, b, fg, zbar, t1, 1.0, true));  // N Q zbar
                 CHK(force(t1, b1v, kap * invN * invN));
-                CHK(flush());
             }
             // 2 Re<bb_k, dT b_{k+1}> = 2 kap (Re<bb_k, dQ Q b_{k+1}> + Re<Q bb_k, dQ b_{k+1}>)
             const S *hk = keep_h ? hb[k - lo] : t2;   // N Q b_{k+1}
@@ -2133,7 +2132,6 @@ int api_backward(ov_ctx *c, int f, const void *x_dev, const void *g_dev, void *g
             CHK(force(bbv[cur], hk, 2.0 * kap * invN * invN));
             CHK(dslash_launch<S>(c, b, fg, bbv[cur], t1, 1.0, true));
             CHK(force(t1, bk1, 2.0 * kap * invN * invN));
-            CHK(flush());   // t1, t2 and bb_{k-1} are overwritten next
             // bb_{k+1} = 2T bb_k - bb_{k-1} = 2 al H t1 - 2 be bb_k - bb_{k-1}, into bb_{k-1}'s buffer
             CHK(dslash_launch<S>(c, b, fg, t1, bbv[prev], 2.0 * al, true, bbv[cur], -2.0 * be, bbv[prev], -1.0));
             std::swap(cur, prev);

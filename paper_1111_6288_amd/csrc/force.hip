@@ -13,8 +13,8 @@
 // projections P-, the second sum_k P+(v(x))_k P+(gamma5 u(x+mu))_k^dag.
 //
 // What bounds it is the accumulator, 576 bytes read and written per site
-// against 384 of a pair of vectors.  A launch therefore takes up to kForcePairs
-// terms with one pass over G, and the four waves of a workgroup take one
+// against 384 of a pair of vectors.  A launch therefore takes the two terms of
+// a recursion step with one pass over G, and the four waves of a workgroup take one
 // direction each of the same 64 sites, which keeps the vectors of a site in
 // one CU's cache and the loads of a thread few.  16^3x32: two terms 59 us,
 // against 2 x 60.5 us for a thread that walked the four directions of one.

@@ -119,7 +119,7 @@ hipError_t launch_small_combine(const double2 *C, const double2 *D, const double
 hipError_t launch_mul_coef(const double2 *C, const double *w, int l, int n, double2 *E, hipStream_t st);
 
 // ---------------------------------------------------------------- backward
-constexpr int kForcePairs = 4;
+constexpr int kForcePairs = 2;   // the two terms of a recursion step
 struct ForceArgs {
     int n;                          // terms, at most kForcePairs
     const double2 *u[kForcePairs];  // planes [12][Vp]
