@@ -1000,15 +1000,16 @@ template <class S>
 int api_dslash(ov_ctx *c, int op, int nrhs, const std::vector<int> &grp, const void *x, void *y)
 {
     const size_t fb = align_up(field_bytes<S>(c) * nrhs);
-    CHK(ws_reserve(c, 2 * fb));
+    const bool canon = dslash_canonical<S>(c, nrhs);   // the kernel writes y itself
+    CHK(ws_reserve(c, canon ? fb : 2 * fb));
     S *X = ws_take<S>(c, field_elems(c) * nrhs);
-    S *Y = ws_take<S>(c, field_elems(c) * nrhs);
+    S *Y = canon ? nullptr : ws_take<S>(c, field_elems(c) * nrhs);
     Batch b;
     CHK(make_batch(c, iota_vec(nrhs), grp, b));
     const int *fg = dev_ints(c, grp);
     HIPCHK(launch_pack_spinor<S>((const double2 *)x, X, (long)field_elems(c), nullptr, nrhs, c->g.V, c->g.Vp,
                                  c->stream));
-    if (dslash_canonical<S>(c, nrhs))   // the kernel writes y itself
+    if (canon)
         return dslash_launch<S>(c, b, fg, X, Y, 1.0, op == OV_OP_HW, nullptr, 0, nullptr, 0, nullptr, 0, (double2 *)y);
     CHK(dslash_launch<S>(c, b, fg, X, Y, 1.0, op == OV_OP_HW));
     HIPCHK(launch_unpack_spinor<S>(Y, (double2 *)y, (long)field_elems(c), nullptr, nrhs, c->g.V, c->g.Vp,
