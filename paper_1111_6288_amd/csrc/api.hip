@@ -543,9 +543,9 @@ int dslash_launch(ov_ctx *c, const Batch &b, const int *fgroup, const S *x, S *y
     const double sb = sizeof(S);
     const int nex = (e1 ? 1 : 0) + (e2 ? 1 : 0) + (e3 ? 1 : 0);
     // compulsory bytes: the links once (two rows of each when rebuilt), every
-    // input and epilogue field once, the output once
-    const double bytes =
-        (double)c->g.V * ((c->recon ? 24.0 : 36.0) * sb + (double)b.n * 12.0 * sb * (2 + nex));
+    // input and epilogue field once, the output once (in its own layout)
+    const double bytes = (double)c->g.V * ((c->recon ? 24.0 : 36.0) * sb +
+                                           (double)b.n * 12.0 * (sb * (1 + nex) + (yc ? 16.0 : sb)));
     if (tu.dir) {
         int pi = prof_begin(c);
         HIPCHK(launch_dslash_dir<S>(d, hw || epi, epi, c->stream));

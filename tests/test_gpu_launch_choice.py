@@ -30,3 +30,20 @@ def test_dslash_reserves_no_output_batch_that_it_does_not_write(L, n, prec):
     ctx.dslash(_x(L, n), prec=prec)
     assert ctx.memory_used() - before < 1.5 * n * 12 * BYTES[prec] * synth.volume(L) + 65536
     ctx.close()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16"])
+@pytest.mark.parametrize("L,n", [((4, 4, 4, 8), 3), ((8, 8, 8, 16), 60)])
+def test_profile_counts_the_bytes_of_the_layout_that_is_written(L, n, prec):
+    """ov_prof_query: two-row links, the packed input and the output, complex128 where the kernel writes the caller's."""
+    ctx = _ctx(L)
+    x = _x(L, n)
+    S, V = BYTES[prec], synth.volume(L)
+    for chosen, out in ((False, 16), (True, S)):
+        if chosen:   # this shape leaves the output to the unpacking pass
+            ctx.set_launch_config(prec, "dslash", rhs_per_thread=2, block=128)
+        ctx.prof_enable(True)
+        ctx.dslash(x, prec=prec)
+        assert ctx.prof_query("dslash")[0::2] == (1, V * (24.0 * S + n * 12.0 * (S + out)))
+        ctx.prof_enable(False)
+    ctx.close()
