@@ -87,6 +87,11 @@ def kernel_source_hash():
     return h.hexdigest()[:16]
 
 
+KERNELS = {"sites": "k_dslash<float2,NR,Q,HW,EPI,REC>", "share_multi": "k_dslash_lds<float2,NR,Q,HW,EPI,REC>",
+           "march": "k_dslash_tm<float2,HW,EPI,W,REC>", "directions": "k_dslash_dir<float2,HW,EPI,REC,NT>",
+           "share": "k_dslash_share<float2,HW,EPI,REC,NT>"}
+
+
 def synth_volume():
     return L[0] * L[1] * L[2] * L[3]
 
@@ -483,7 +488,10 @@ def main():
     if not args.autotune:
         ctx.load_tuning(TUNING_FILE, "fp64", nrhs)
         ctx.load_tuning(TUNING_FILE, "bf16", nrhs)
-    tuned = {k: ctx.get_launch_config("fp32", k) for k in ("dslash", "clenshaw")}
+    plan = {k: ctx.launch_plan("fp32", k, nrhs) for k in ("dslash", "clenshaw")}
+    # the shape in use: as recorded where one is, as the library's own rule has it otherwise
+    tuned = {k: ctx.get_launch_config("fp32", k) if p["chosen"]
+             else {f: v for f, v in p.items() if f not in ("kernel", "chosen")} for k, p in plan.items()}
     print(f"[bench] setup {t_setup:.1f}s, fp32 tuning {tuned}", file=sys.stderr, flush=True)
 
     y32 = torch.empty_like(x)
@@ -532,11 +540,7 @@ def main():
                 "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "copy_GBps": round(copy_bw / 1e9, 1), "frac_of_copy": round(achieved / (copy_bw / 1e9), 4),
                 "traffic": traffic, "traffic_bytes_per_launch": traffic_bytes,
-                "kernel": ("k_dslash_tm<float2,HW,EPI,W,REC> (t-marching dslash + fused Clenshaw epilogue)"
-                           if tuned["clenshaw"]["site_order"] == 2
-                           else "k_dslash_share<float2,HW,EPI,REC,NT> (dslash with LDS-shared links + fused "
-                                "Clenshaw epilogue)" if tuned["clenshaw"].get("wshare", 1) > 1
-                           else "k_dslash<float2,NR,Q,HW,EPI,REC> (dslash + fused Clenshaw epilogue)"),
+                "kernel": KERNELS[plan["clenshaw"]["kernel"]] + " (dslash + fused Clenshaw epilogue)",
                 "two_row_links": two_row,
                 "launches": n_launch, "avg_ms": round(avg_ms, 4),
                 "algorithmic_bytes_per_launch": bytes_per_launch}

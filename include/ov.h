@@ -517,6 +517,22 @@ int ov_set_occupancy(ov_ctx *ctx, int prec, int blocks_per_cu);
  * OV_EINVAL on a value out of range (nothing changed). */
 int ov_get_launch_config(ov_ctx *ctx, int prec, int kind, int cfg[8]);
 int ov_set_launch_config(ov_ctx *ctx, int prec, int kind, const int cfg[8]);
+/* What a launch of `kind` with nrhs right-hand sides runs: plan = {kernel
+ * (OV_KERNEL_*), 1 if by a chosen shape and 0 if by the library's own rule,
+ * rhs_per_thread, threads per workgroup, site_order, blocks_per_cu,
+ * stream_hint, rhs_split, cols, wshare}, after the adjustments to the batch
+ * and the lattice.  (ov_get_launch_config and ov_get_tuning return what was
+ * stored by a setter or the search, or the defaults, whether or not it is in
+ * use.)  A plain launch of ov_dslash that writes the caller's array takes 256
+ * threads where the direction waves are reported with 512. */
+enum {
+    OV_KERNEL_SITES = 0,       /* a thread per site, rhs_per_thread right-hand sides */
+    OV_KERNEL_SHARE_MULTI = 1, /* wshare waves share staged links, several right-hand sides each */
+    OV_KERNEL_MARCH = 2,       /* t-marching */
+    OV_KERNEL_DIRECTIONS = 3,  /* a wave per hop or direction */
+    OV_KERNEL_SHARE = 4        /* wshare waves share staged links, one right-hand side each */
+};
+int ov_get_launch_plan(ov_ctx *ctx, int prec, int kind, int nrhs, int plan[10]);
 int ov_autotune(ov_ctx *ctx, int prec, int nrhs, const char *cache_path);
 
 /*

@@ -492,13 +492,25 @@ ov_ctx::Launch launch_rule(const Geo &g, int n)
     return t;
 }
 
+// What a launch of the given kind (0: plain, 1: fused epilogue) of n right-hand sides runs.
+template <class S>
+ov_ctx::Launch launch_plan(const ov_ctx *c, int kind, int n)
+{
+    const ov_ctx::Launch &set = c->tune[PrecOf<S>::p][kind];
+    ov_ctx::Launch t = set.chosen ? set : launch_rule<S>(c->g, n);
+    if (t.dir) return t;
+    while (t.split > 1 && (t.split / 2) * t.nr >= n) t.split /= 2;
+    while (t.nr > 1 && t.nr / 2 >= n) t.nr /= 2;
+    while (t.wshare > 1 && (t.wshare / 2) * t.split * t.nr >= n && t.chosen) t.wshare /= 2;   // no wave without a RHS
+    return t;
+}
+
 // Whether a plain launch of n right-hand sides can write the canonical layout (dslash_launch's yc).
 template <class S>
 bool dslash_canonical(const ov_ctx *c, int n)
 {
-    if (c->tune[PrecOf<S>::p][0].chosen) return false;
-    const ov_ctx::Launch t = launch_rule<S>(c->g, n);
-    return t.dir || t.wshare > 1;
+    const ov_ctx::Launch t = launch_plan<S>(c, 0, n);
+    return !t.chosen && (t.dir || t.wshare > 1);
 }
 
 template <class S>
@@ -526,9 +538,8 @@ int dslash_launch(ov_ctx *c, const Batch &b, const int *fgroup, const S *x, S *y
     d.c1 = c1;
     d.c2 = c2;
     d.c3 = c3;
-    const int P = PrecOf<S>::p;
     const bool epi = e1 || e2 || e3;
-    const auto tu = c->tune[P][epi ? 1 : 0].chosen ? c->tune[P][epi ? 1 : 0] : launch_rule<S>(c->g, b.n);
+    const ov_ctx::Launch tu = launch_plan<S>(c, epi ? 1 : 0, b.n);
     d.order = tu.order;
     d.blocks_per_cu = tu.cap;
     d.stream_hint = tu.stream_hint;
@@ -552,13 +563,9 @@ int dslash_launch(ov_ctx *c, const Batch &b, const int *fgroup, const S *x, S *y
         prof_end(c, pi, epi ? PC_CLENSHAW : PC_DSLASH, bytes);
         return OV_OK;
     }
-    int nr = tu.nr, split = tu.split, ws = tu.wshare;
-    while (split > 1 && (split / 2) * nr >= b.n) split /= 2;
-    while (nr > 1 && nr / 2 >= b.n) nr /= 2;
-    while (ws > 1 && (ws / 2) * split * nr >= b.n && tu.chosen) ws /= 2;   // no wave without a RHS
-    d.wshare = ws;
+    d.wshare = tu.wshare;
     int pi = prof_begin(c);
-    HIPCHK(launch_dslash<S>(d, hw || epi, epi, nr, tu.block, split, c->stream));
+    HIPCHK(launch_dslash<S>(d, hw || epi, epi, tu.nr, tu.block, tu.split, c->stream));
     prof_end(c, pi, epi ? PC_CLENSHAW : PC_DSLASH, bytes);
     return OV_OK;
 }
@@ -1604,6 +1611,39 @@ int ov_set_launch_config(ov_ctx *c, int prec, int kind, const int *cfg)
     tu.cols = cl;
     tu.wshare = ws;
     tu.chosen = true;
+    return OV_OK;
+}
+
+int ov_get_launch_plan(ov_ctx *c, int prec, int kind, int nrhs, int *plan)
+{
+    CHK(check_ctx(c));
+    CHK(check_prec(c, prec));
+    if (kind != 0 && kind != 1) return fail(c, OV_EINVAL, "kind must be 0 (plain) or 1 (fused epilogue)");
+    if (nrhs < 1) return fail(c, OV_EINVAL, "nrhs must be at least 1");
+    if (!plan) return fail(c, OV_EINVAL, "plan is NULL");
+    const ov_ctx::Launch t = prec == OV_FP64   ? launch_plan<double2>(c, kind, nrhs)
+                             : prec == OV_FP32 ? launch_plan<float2>(c, kind, nrhs)
+                                               : launch_plan<uint32_t>(c, kind, nrhs);
+    const Geo &g = c->g;
+    const bool whole = g.V % 64 == 0, march = t.order == 2 && whole;   // as the launchers decide
+    const int kernel = t.dir             ? OV_KERNEL_DIRECTIONS
+                       : march           ? OV_KERNEL_MARCH
+                       : t.wshare <= 1   ? OV_KERNEL_SITES
+                       : t.nr * t.split == 1 ? OV_KERNEL_SHARE
+                                             : OV_KERNEL_SHARE_MULTI;
+    plan[0] = kernel;
+    plan[1] = t.chosen ? 1 : 0;
+    plan[2] = t.nr;
+    plan[3] = t.dir ? 64 * dir_waves(t.stream_hint != 0, false)
+              : march ? (t.block == 512 ? 512 : 256)
+              : t.wshare > 1 ? 64 * t.wshare
+                             : std::min(t.block, 256);
+    plan[4] = march || (whole && ((t.order == 1 && g.Lz % 8 == 0) || (t.order == 3 && g.Lt % 8 == 0))) ? t.order : 0;
+    plan[5] = t.cap;
+    plan[6] = t.stream_hint;
+    plan[7] = t.split;
+    plan[8] = t.cols;
+    plan[9] = march ? 1 : t.wshare;
     return OV_OK;
 }
 

@@ -169,16 +169,14 @@ __device__ __forceinline__ cx<R> sum_hops(const cx<R> *__restrict__ g)
 // CAN: the output goes to the canonical layout (12 numbers per site, rows of 13
 // in the LDS of the hops, which have been summed by then) instead of a field.
 //
-// Eight waves, one hop each, have half the loads and arithmetic of a hop pair
-// in a row; four waves are fewer to start and to meet at the barrier.  Mean of
+// dir_waves: eight waves, one hop each, have half the loads and arithmetic of a
+// hop pair in a row; four waves are fewer to start and to meet at the barrier.  Mean of
 // a plain and a fused launch, four / eight waves:
 //   FP64 12 RHS of 4^4 5.0 / 4.7 us, FP32 5 RHS of 6x5x7x10 4.8 / 4.4, FP32 4 RHS of 8^3x16 6.5 / 6.1,
 //   FP64 4 RHS of 8^3x16 8.7 / 8.2, of 12^3x24 32.1 / 29.4, FP64 1 RHS of 16^3x32 28.9 / 27.3,
 // but in batches that stream past the caches four read less again:
 //   FP64 1 RHS of 24^3x48 159 / 163, 2 RHS 294 / 307, FP32 2 RHS 139 / 141,
 // and a single call with canonical output is 10.2 / 10.4 us on 8^3x16.
-constexpr int dir_waves(bool NT, bool CAN) { return NT || CAN ? 4 : 8; }
-
 template <class S, bool HW, bool EPI, bool REC, bool NT, bool CAN>
 __global__ __launch_bounds__(dir_waves(NT, CAN) * 64, dir_waves(NT, CAN) == 8 && !(sizeof(S) == 16 && !REC) ? 4 : 2)
 void k_dslash_dir(DsArgs<S> a)

@@ -44,6 +44,8 @@ template <class S>
 hipError_t launch_dslash_share(const DsArgs<S> &a, bool hw, bool epi, hipStream_t st);
 // the direction-wave kernel (site orders 0, 1 and 3); its grid holds the site blocks of an XCD in y
 inline bool dslash_dir_fits(const Geo &g) { return (g.Vp / 64 + 7) / 8 <= 65535; }
+// its waves per workgroup: nt with the stream hint, canon with the canonical output (times: dslash_dir.hip)
+constexpr int dir_waves(bool nt, bool canon) { return nt || canon ? 4 : 8; }
 template <class S>
 hipError_t launch_dslash_dir(const DsArgs<S> &a, bool hw, bool epi, hipStream_t st);
 

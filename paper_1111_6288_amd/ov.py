@@ -108,6 +108,7 @@ def _load():
         "ov_set_occupancy": ([vp, i, i], i),
         "ov_get_launch_config": ([vp, i, i, cp(i)], i),
         "ov_set_launch_config": ([vp, i, i, cp(i)], i),
+        "ov_get_launch_plan": ([vp, i, i, i, cp(i)], i),
         "ov_dslash_noalloc": ([vp, i, i, i, cp(i), vp, vp], i),
         "ov_set_norm_check": ([vp, i], i),
         "ov_norm_status": ([vp], i),
@@ -132,7 +133,7 @@ EXPORTED = ("ov_create", "ov_destroy", "ov_set_stream", "ov_last_error", "ov_upl
             "ov_set_launch_config", "ov_hw_eigensolve", "ov_dense_heev", "ov_multishift_cg",
             "ov_dov_eigensolve", "ov_timeslice_norm2", "ov_correlator_deta", "ov_set_link_reconstruct",
             "ov_get_link_format", "ov_dslash_noalloc", "ov_set_norm_check", "ov_norm_status", "ov_get_sign_norm",
-            "ov_pion_correlator", "ov_ratio_R", "ov_set_adjoint_memory")
+            "ov_pion_correlator", "ov_ratio_R", "ov_set_adjoint_memory", "ov_get_launch_plan")
 
 
 def _ints(v):
@@ -488,7 +489,8 @@ class Context:
     _CFG = ("rhs_per_thread", "block", "site_order", "blocks_per_cu", "stream_hint", "rhs_split", "cols", "wshare")
 
     def get_launch_config(self, prec, kind="dslash"):
-        """Launch shape of the plain ("dslash") or fused-epilogue ("clenshaw") launches of prec."""
+        """Stored launch shape of the plain ("dslash") or fused-epilogue ("clenshaw") launches of prec, in use or
+        not (launch_plan says what runs)."""
         cfg = (C.c_int * len(self._CFG))()
         self._chk(lib.ov_get_launch_config(self._h, PREC[prec], self._KIND[kind], cfg))
         return dict(zip(self._CFG, list(cfg)))
@@ -502,6 +504,14 @@ class Context:
             cur[k] = int(v)
         arr = (C.c_int * len(self._CFG))(*[cur[k] for k in self._CFG])
         return self._chk(lib.ov_set_launch_config(self._h, PREC[prec], self._KIND[kind], arr))
+
+    _KERNEL = ("sites", "share_multi", "march", "directions", "share")
+
+    def launch_plan(self, prec, kind, nrhs):
+        """What a launch of this kind and batch size runs (ov_get_launch_plan): kernel, chosen, and the shape."""
+        p = (C.c_int * (2 + len(self._CFG)))()
+        self._chk(lib.ov_get_launch_plan(self._h, PREC[prec], self._KIND[kind], int(nrhs), p))
+        return {"kernel": self._KERNEL[p[0]], "chosen": bool(p[1]), **dict(zip(self._CFG, list(p)[2:]))}
 
     def get_tuning(self, prec):
         a, b = C.c_int(), C.c_int()

@@ -47,3 +47,30 @@ def test_profile_counts_the_bytes_of_the_layout_that_is_written(L, n, prec):
         assert ctx.prof_query("dslash")[0::2] == (1, V * (24.0 * S + n * 12.0 * (S + out)))
         ctx.prof_enable(False)
     ctx.close()
+
+
+def test_launch_plan_names_what_runs():
+    ctx = _ctx((8, 8, 8, 16))
+    kernel = {(p, n): ctx.launch_plan(p, "dslash", n)["kernel"] for p in BYTES for n in (1, 2, 12, 60)}
+    assert kernel["fp64", 2] == kernel["fp32", 12] == kernel["bf16", 12] == "directions"   # small batches
+    assert kernel["fp64", 60] == kernel["fp32", 60] == kernel["bf16", 60] == "share"       # more than the caches hold
+    stored = ctx.get_launch_config("fp32", "clenshaw")
+    assert not any(ctx.launch_plan(p, k, n)["chosen"] for p in BYTES for k in ("dslash", "clenshaw") for n in (1, 60))
+    assert ctx.get_launch_config("fp32", "clenshaw") == stored
+    for cfg, name in ((dict(rhs_per_thread=2, block=512), "sites"), (dict(rhs_per_thread=1, wshare=8), "share"),
+                      (dict(rhs_per_thread=2, wshare=4), "share_multi"), (dict(site_order=2, wshare=1), "march")):
+        ctx.set_launch_config("fp32", "clenshaw", **cfg)
+        p = ctx.launch_plan("fp32", "clenshaw", 60)
+        assert p["chosen"] and p["kernel"] == name
+    # the shape follows the batch and the lattice: two vectors need no eight waves, a z extent of 4 no slabs
+    ctx.set_launch_config("fp32", "clenshaw", rhs_per_thread=1, wshare=8, site_order=1)
+    assert ctx.launch_plan("fp32", "clenshaw", 2)["wshare"] == 2
+    ctx.close()
+    ctx = _ctx((8, 8, 4, 16))
+    ctx.set_launch_config("fp32", "dslash", site_order=1)
+    assert ctx.launch_plan("fp32", "dslash", 2)["site_order"] == 0
+    assert not ctx.launch_plan("fp32", "clenshaw", 2)["chosen"]
+    for bad in (("fp32", "dslash", 0),):
+        with pytest.raises(Exception):
+            ctx.launch_plan(*bad)
+    ctx.close()
