@@ -477,9 +477,10 @@ int ov_prof_query(ov_ctx *ctx, const char *kernel_class, long *launches, double 
  * separately for plain launches and for launches with the fused Clenshaw
  * epilogue, keeps the fastest of each and, with a non-NULL cache_path,
  * appends one JSON line per kind there.  ov_get_tuning reports the plain
- * kind.  Until one of these setters or ov_autotune chooses a shape, every
- * launch takes a kernel by the batch and the lattice; ov_autotune keeps that
- * (and records its time as ms_unchosen) where no shape is faster.
+ * kind.  Until ov_set_tuning, ov_set_launch_config, ov_autotune or one of the
+ * two setters below with another value than the one in place chooses a shape,
+ * every launch takes a kernel by the batch and the lattice; ov_autotune keeps
+ * that (and records its time as ms_unchosen) where no shape is faster.
  */
 int ov_set_tuning(ov_ctx *ctx, int prec, int rhs_per_thread, int block);
 int ov_get_tuning(ov_ctx *ctx, int prec, int *rhs_per_thread, int *block);

@@ -1543,8 +1543,8 @@ int ov_set_site_order(ov_ctx *c, int prec, int order)
     if (order < 0 || order > 3) return fail(c, OV_EINVAL, "site order must be 0, 1, 2 or 3");
     invalidate_graphs(c);
     for (auto &tu : c->tune[prec]) {
+        tu.chosen = tu.chosen || tu.order != order;   // the value that is there chooses nothing
         tu.order = order;
-        tu.chosen = true;
     }
     return OV_OK;
 }
@@ -1556,8 +1556,8 @@ int ov_set_occupancy(ov_ctx *c, int prec, int blocks_per_cu)
     if (blocks_per_cu < 0 || blocks_per_cu > 32) return fail(c, OV_EINVAL, "blocks_per_cu outside [0, 32]");
     invalidate_graphs(c);
     for (auto &tu : c->tune[prec]) {
+        tu.chosen = tu.chosen || tu.cap != blocks_per_cu;
         tu.cap = blocks_per_cu;
-        tu.chosen = true;
     }
     return OV_OK;
 }

@@ -74,3 +74,19 @@ def test_launch_plan_names_what_runs():
         with pytest.raises(Exception):
             ctx.launch_plan(*bad)
     ctx.close()
+
+
+def test_setting_the_value_in_place_chooses_nothing():
+    ctx = _ctx((8, 8, 8, 16))
+    rule = ctx.launch_plan("fp32", "clenshaw", 4)
+    ctx.set_site_order("fp32", 0)
+    ctx.set_occupancy("fp32", 0)
+    assert ctx.launch_plan("fp32", "clenshaw", 4) == rule and not rule["chosen"]
+    ctx.set_occupancy("fp32", 2)
+    plan = ctx.launch_plan("fp32", "clenshaw", 4)
+    assert plan["chosen"] and plan["blocks_per_cu"] == 2
+    ctx.set_site_order("fp32", 0)   # nor does it take a choice back
+    assert ctx.launch_plan("fp32", "clenshaw", 4) == plan
+    ctx.set_site_order("fp64", 1)
+    assert ctx.launch_plan("fp64", "dslash", 4)["site_order"] == 1
+    ctx.close()
