@@ -518,6 +518,12 @@ int ov_set_occupancy(ov_ctx *ctx, int prec, int blocks_per_cu);
  * OV_EINVAL on a value out of range (nothing changed). */
 int ov_get_launch_config(ov_ctx *ctx, int prec, int kind, int cfg[8]);
 int ov_set_launch_config(ov_ctx *ctx, int prec, int kind, const int cfg[8]);
+/* Which batches the shape chosen for `kind` governs: nrhs > 0 those within a
+ * factor of two of nrhs (n > nrhs / 2 and n < 2 nrhs; the batch it was
+ * measured for), 0 all (as every setter that chooses and ov_autotune leave
+ * it), -1 none: the choice is dropped.  The library's own rule takes the
+ * others. */
+int ov_set_launch_batch(ov_ctx *ctx, int prec, int kind, int nrhs);
 /* What a launch of `kind` with nrhs right-hand sides runs: plan = {kernel
  * (OV_KERNEL_*), 1 if by a chosen shape and 0 if by the library's own rule,
  * rhs_per_thread, threads per workgroup, site_order, blocks_per_cu,

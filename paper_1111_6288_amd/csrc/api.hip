@@ -121,6 +121,7 @@ struct ov_ctx {
     struct Launch {
         int nr = 2, block = 128, order = 0, cap = 0, stream_hint = 0, split = 1, cols = 1, wshare = 1;
         bool chosen = false;   // set by the caller or the autotuner; otherwise launch_rule decides per batch
+        int batch = 0;         // a chosen shape is for batches within a factor of two of this; 0: for all
         bool dir = false;      // direction waves (launch_rule only)
     };
     Launch tune[3][2];
@@ -497,7 +498,8 @@ template <class S>
 ov_ctx::Launch launch_plan(const ov_ctx *c, int kind, int n)
 {
     const ov_ctx::Launch &set = c->tune[PrecOf<S>::p][kind];
-    ov_ctx::Launch t = set.chosen ? set : launch_rule<S>(c->g, n);
+    const bool use = set.chosen && (set.batch == 0 || (2L * n > set.batch && n < 2L * set.batch));
+    ov_ctx::Launch t = use ? set : launch_rule<S>(c->g, n);
     if (t.dir) return t;
     while (t.split > 1 && (t.split / 2) * t.nr >= n) t.split /= 2;
     while (t.nr > 1 && t.nr / 2 >= n) t.nr /= 2;
@@ -1532,6 +1534,7 @@ int ov_set_tuning(ov_ctx *c, int prec, int rhs_per_thread, int block)
         tu.wshare = 1;
         if (rhs_per_thread > 2) tu.split = 1;
         tu.chosen = true;
+        tu.batch = 0;
     }
     return OV_OK;
 }
@@ -1543,8 +1546,10 @@ int ov_set_site_order(ov_ctx *c, int prec, int order)
     if (order < 0 || order > 3) return fail(c, OV_EINVAL, "site order must be 0, 1, 2 or 3");
     invalidate_graphs(c);
     for (auto &tu : c->tune[prec]) {
-        tu.chosen = tu.chosen || tu.order != order;   // the value that is there chooses nothing
+        if (tu.order == order) continue;   // the value that is there chooses nothing
         tu.order = order;
+        tu.chosen = true;
+        tu.batch = 0;
     }
     return OV_OK;
 }
@@ -1556,8 +1561,10 @@ int ov_set_occupancy(ov_ctx *c, int prec, int blocks_per_cu)
     if (blocks_per_cu < 0 || blocks_per_cu > 32) return fail(c, OV_EINVAL, "blocks_per_cu outside [0, 32]");
     invalidate_graphs(c);
     for (auto &tu : c->tune[prec]) {
-        tu.chosen = tu.chosen || tu.cap != blocks_per_cu;
+        if (tu.cap == blocks_per_cu) continue;
         tu.cap = blocks_per_cu;
+        tu.chosen = true;
+        tu.batch = 0;
     }
     return OV_OK;
 }
@@ -1611,6 +1618,20 @@ int ov_set_launch_config(ov_ctx *c, int prec, int kind, const int *cfg)
     tu.cols = cl;
     tu.wshare = ws;
     tu.chosen = true;
+    tu.batch = 0;
+    return OV_OK;
+}
+
+int ov_set_launch_batch(ov_ctx *c, int prec, int kind, int nrhs)
+{
+    CHK(check_ctx(c));
+    CHK(check_prec(c, prec));
+    if (kind != 0 && kind != 1) return fail(c, OV_EINVAL, "kind must be 0 (plain) or 1 (fused epilogue)");
+    if (nrhs < -1) return fail(c, OV_EINVAL, "nrhs must be a batch size, 0 (all) or -1 (none)");
+    invalidate_graphs(c);
+    auto &tu = c->tune[prec][kind];
+    if (nrhs < 0) tu.chosen = false;
+    tu.batch = std::max(nrhs, 0);
     return OV_OK;
 }
 
@@ -2357,6 +2378,7 @@ int ov_autotune(ov_ctx *c, int prec, int nrhs, const char *cache_path)
             };
             // the kernel taken when no shape is chosen; it stays unless a shape beats it
             tu.chosen = false;
+            tu.batch = 0;
             float own = 0;
             rc = timed(&own);
             tu.chosen = true;

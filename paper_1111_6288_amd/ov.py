@@ -108,6 +108,7 @@ def _load():
         "ov_set_occupancy": ([vp, i, i], i),
         "ov_get_launch_config": ([vp, i, i, cp(i)], i),
         "ov_set_launch_config": ([vp, i, i, cp(i)], i),
+        "ov_set_launch_batch": ([vp, i, i, i], i),
         "ov_get_launch_plan": ([vp, i, i, i, cp(i)], i),
         "ov_dslash_noalloc": ([vp, i, i, i, cp(i), vp, vp], i),
         "ov_set_norm_check": ([vp, i], i),
@@ -133,7 +134,8 @@ EXPORTED = ("ov_create", "ov_destroy", "ov_set_stream", "ov_last_error", "ov_upl
             "ov_set_launch_config", "ov_hw_eigensolve", "ov_dense_heev", "ov_multishift_cg",
             "ov_dov_eigensolve", "ov_timeslice_norm2", "ov_correlator_deta", "ov_set_link_reconstruct",
             "ov_get_link_format", "ov_dslash_noalloc", "ov_set_norm_check", "ov_norm_status", "ov_get_sign_norm",
-            "ov_pion_correlator", "ov_ratio_R", "ov_set_adjoint_memory", "ov_get_launch_plan")
+            "ov_pion_correlator", "ov_ratio_R", "ov_set_adjoint_memory", "ov_get_launch_plan",
+            "ov_set_launch_batch")
 
 
 def _ints(v):
@@ -505,6 +507,10 @@ class Context:
         arr = (C.c_int * len(self._CFG))(*[cur[k] for k in self._CFG])
         return self._chk(lib.ov_set_launch_config(self._h, PREC[prec], self._KIND[kind], arr))
 
+    def set_launch_batch(self, prec, kind, nrhs):
+        """Batches that a chosen shape governs: those near nrhs, all (0) or none (-1) (ov_set_launch_batch)."""
+        return self._chk(lib.ov_set_launch_batch(self._h, PREC[prec], self._KIND[kind], int(nrhs)))
+
     _KERNEL = ("sites", "share_multi", "march", "directions", "share")
 
     def launch_plan(self, prec, kind, nrhs):
@@ -522,10 +528,11 @@ class Context:
         return self._chk(lib.ov_autotune(self._h, PREC[prec], int(nrhs),
                                          cache_path.encode() if cache_path else None))
 
-    def load_tuning(self, path, prec, nrhs):
+    def load_tuning(self, path, prec, nrhs, near_only=False):
         """Apply the launch shapes recorded by autotune (one JSON object per line) for this
         lattice, precision, batch size and link format (records without a format match
-        either); returns the kinds applied (empty if none match)."""
+        either); returns the kinds applied (empty if none match).  They govern batches of
+        every size, or with near_only those within a factor of two of nrhs."""
         import json
         applied = []
         two_row = self.link_format()[0]
@@ -547,5 +554,7 @@ class Context:
             defaults = {"stream_hint": 0, "rhs_split": 1, "cols": 1, "wshare": 1}
             self.set_launch_config(prec, e["kind"], **{k: e.get(k, defaults.get(k)) for k in self._CFG
                                                        if k in e or k in defaults})
+            if near_only:
+                self.set_launch_batch(prec, e["kind"], nrhs)
             applied.append(e["kind"])
         return applied

@@ -90,3 +90,34 @@ def test_setting_the_value_in_place_chooses_nothing():
     ctx.set_site_order("fp64", 1)
     assert ctx.launch_plan("fp64", "dslash", 4)["site_order"] == 1
     ctx.close()
+
+
+def test_a_shape_can_be_limited_to_its_batch_and_dropped(tmp_path):
+    L, n = (8, 8, 8, 16), 24
+    ctx = _ctx(L)
+    x = _x(L, 30)
+    rule = {m: ctx.launch_plan("fp64", "dslash", m) for m in (1, 12, 13, 24, 47, 48)}
+    ref = {m: ctx.dslash(x[:m].contiguous()) for m in (12, 24)}
+    ctx.set_launch_config("fp64", "dslash", rhs_per_thread=2, block=64)
+    assert all(ctx.launch_plan("fp64", "dslash", m)["chosen"] for m in rule)   # a setter speaks of every batch
+    ctx.set_launch_batch("fp64", "dslash", n)
+    for m, p in rule.items():
+        q = ctx.launch_plan("fp64", "dslash", m)
+        assert (q["chosen"] and q["block"] == 64) if 12 < m < 48 else q == p
+    for m, y in ref.items():   # 12 vectors by the rule, 24 by the shape
+        assert torch.equal(ctx.dslash(x[:m].contiguous()), y)
+    ctx.set_launch_config("fp64", "dslash", block=128)
+    assert ctx.launch_plan("fp64", "dslash", 1)["chosen"]
+    ctx.set_launch_batch("fp64", "dslash", -1)
+    assert all(ctx.launch_plan("fp64", "dslash", m) == p for m, p in rule.items())
+    with pytest.raises(Exception):
+        ctx.set_launch_batch("fp64", "dslash", -2)
+    # a record, limited to its batch and not
+    rec = tmp_path / "shapes.jsonl"
+    rec.write_text('{"arch": "gfx950", "L": [8, 8, 8, 16], "prec": 0, "nrhs": 24, "kind": "dslash", "rhs_per_thread": 2, '
+                   '"block": 64, "site_order": 0, "blocks_per_cu": 0, "ms_per_launch": 0.1}\n')
+    assert ctx.load_tuning(str(rec), "fp64", n, near_only=True) == ["dslash"]
+    assert [ctx.launch_plan("fp64", "dslash", m)["chosen"] for m in (1, 24)] == [False, True]
+    assert ctx.load_tuning(str(rec), "fp64", n) == ["dslash"]
+    assert [ctx.launch_plan("fp64", "dslash", m)["chosen"] for m in (1, 24)] == [True, True]
+    ctx.close()
