@@ -531,8 +531,10 @@ class Context:
     def load_tuning(self, path, prec, nrhs, near_only=False):
         """Apply the launch shapes recorded by autotune (one JSON object per line) for this
         lattice, precision, batch size and link format (records without a format match
-        either); returns the kinds applied (empty if none match).  They govern batches of
-        every size, or with near_only those within a factor of two of nrhs."""
+        either); returns the kinds applied (empty if none match).  Of several records of a
+        kind the last one holds, also where it says that no shape beat the library's own
+        choice.  Shapes govern batches of every size, or with near_only those within a factor
+        of two of nrhs."""
         import json
         applied = []
         two_row = self.link_format()[0]
@@ -549,7 +551,8 @@ class Context:
                     or bool(e.get("two_row_links", two_row)) != two_row):
                 continue
             if "ms_unchosen" in e and e["ms_unchosen"] <= e["ms_per_launch"]:
-                applied.append(e["kind"])   # no shape beat the library's own choice: leave it
+                self.set_launch_batch(prec, e["kind"], -1)   # no shape beat the library's own choice
+                applied.append(e["kind"])
                 continue
             defaults = {"stream_hint": 0, "rhs_split": 1, "cols": 1, "wshare": 1}
             self.set_launch_config(prec, e["kind"], **{k: e.get(k, defaults.get(k)) for k in self._CFG

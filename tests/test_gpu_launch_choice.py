@@ -121,3 +121,20 @@ def test_a_shape_can_be_limited_to_its_batch_and_dropped(tmp_path):
     assert ctx.load_tuning(str(rec), "fp64", n) == ["dslash"]
     assert [ctx.launch_plan("fp64", "dslash", m)["chosen"] for m in (1, 24)] == [True, True]
     ctx.close()
+
+
+def test_the_last_record_of_a_kind_holds(tmp_path):
+    ctx = _ctx((8, 8, 8, 16))
+    rule = ctx.launch_plan("fp32", "clenshaw", 24)
+    head = '{"arch": "gfx950", "L": [8, 8, 8, 16], "prec": 1, "nrhs": 24, "kind": "clenshaw", "rhs_per_thread": 2, '
+    shape = head + '"block": 64, "site_order": 0, "blocks_per_cu": 0, "ms_per_launch": 0.1, "ms_unchosen": 0.2}\n'
+    keep = head + '"block": 256, "site_order": 0, "blocks_per_cu": 0, "ms_per_launch": 0.2, "ms_unchosen": 0.1}\n'
+    rec = tmp_path / "shapes.jsonl"
+    rec.write_text(shape + keep)
+    ctx.set_launch_config("fp32", "clenshaw", rhs_per_thread=4, block=128)   # nor does an earlier choice stay
+    assert "clenshaw" in ctx.load_tuning(str(rec), "fp32", 24)
+    assert ctx.launch_plan("fp32", "clenshaw", 24) == rule
+    rec.write_text(keep + shape)
+    assert "clenshaw" in ctx.load_tuning(str(rec), "fp32", 24)
+    assert ctx.launch_plan("fp32", "clenshaw", 24)["block"] == 64
+    ctx.close()
