@@ -480,7 +480,8 @@ int ov_prof_query(ov_ctx *ctx, const char *kernel_class, long *launches, double 
  * kind.  Until ov_set_tuning, ov_set_launch_config, ov_autotune or one of the
  * two setters below with another value than the one in place chooses a shape,
  * every launch takes a kernel by the batch and the lattice; ov_autotune keeps
- * that (and records its time as ms_unchosen) where no shape is faster.
+ * that where no shape is faster by 2 % (its records give the time as
+ * ms_unchosen, and what was kept as chosen, 1 or 0).
  */
 int ov_set_tuning(ov_ctx *ctx, int prec, int rhs_per_thread, int block);
 int ov_get_tuning(ov_ctx *ctx, int prec, int *rhs_per_thread, int *block);

@@ -2376,12 +2376,8 @@ int ov_autotune(ov_ctx *c, int prec, int nrhs, const char *cache_path)
                     return OV_EHIP;
                 return OV_OK;
             };
-            // the kernel taken when no shape is chosen; it stays unless a shape beats it
-            tu.chosen = false;
-            tu.batch = 0;
-            float own = 0;
-            rc = timed(&own);
             tu.chosen = true;
+            tu.batch = 0;
             for (int sh = 0; sh < 2 && rc == OV_OK; ++sh)
             for (int od = 0; od < 4 && rc == OV_OK; ++od)
             for (int cl : colss)
@@ -2421,8 +2417,21 @@ int ov_autotune(ov_ctx *c, int prec, int nrhs, const char *cache_path)
                     }
                 }
             }
+            // The winner has the luckiest of hundreds of short runs.  It is timed again, in turn with the
+            // kernel that is taken when no shape is chosen, which stays unless the shape is ahead by more
+            // than such runs differ (about 1 %).
+            best = 1e30f;
+            float own = 1e30f;
+            for (int r = 0; r < 10 && rc == OV_OK; ++r) {
+                float ms = 0;
+                tu = bestc;
+                tu.chosen = r % 2 == 0;
+                rc = timed(&ms);
+                float &m = tu.chosen ? best : own;
+                m = std::min(m, ms);
+            }
             tu = rc == OV_OK ? bestc : keep;
-            if (rc == OV_OK) tu.chosen = best < own;
+            if (rc == OV_OK) tu.chosen = best < 0.98f * own;
             best_ms[kind] = best / (float)reps;
             own_ms[kind] = own / (float)reps;
         }
@@ -2440,10 +2449,11 @@ int ov_autotune(ov_ctx *c, int prec, int nrhs, const char *cache_path)
                                  "{\"arch\": \"gfx950\", \"L\": [%d, %d, %d, %d], \"prec\": %d, \"nrhs\": %d, "
                                  "\"kind\": \"%s\", \"rhs_per_thread\": %d, \"block\": %d, \"site_order\": %d, "
                                  "\"blocks_per_cu\": %d, \"stream_hint\": %d, \"rhs_split\": %d, \"cols\": %d, "
-                                 "\"wshare\": %d, \"two_row_links\": %d, \"ms_per_launch\": %.6f, \"ms_unchosen\": %.6f}\n",
+                                 "\"wshare\": %d, \"two_row_links\": %d, \"ms_per_launch\": %.6f, \"ms_unchosen\": %.6f, "
+                                 "\"chosen\": %d}\n",
                                  c->L[0], c->L[1], c->L[2], c->L[3], prec, nrhs, kind ? "clenshaw" : "dslash",
                                  tu.nr, tu.block, tu.order, tu.cap, tu.stream_hint, tu.split, tu.cols, tu.wshare,
-                                 c->recon ? 1 : 0, best_ms[kind], own_ms[kind]);
+                                 c->recon ? 1 : 0, best_ms[kind], own_ms[kind], tu.chosen ? 1 : 0);
                 }
                 std::fclose(fp);
             }

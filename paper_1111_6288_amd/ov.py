@@ -550,7 +550,7 @@ class Context:
                     or e.get("nrhs") != int(nrhs) or e.get("kind") not in self._KIND
                     or bool(e.get("two_row_links", two_row)) != two_row):
                 continue
-            if "ms_unchosen" in e and e["ms_unchosen"] <= e["ms_per_launch"]:
+            if not e.get("chosen", "ms_unchosen" not in e or e["ms_unchosen"] > e["ms_per_launch"]):
                 self.set_launch_batch(prec, e["kind"], -1)   # no shape beat the library's own choice
                 applied.append(e["kind"])
                 continue

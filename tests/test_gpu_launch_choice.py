@@ -138,3 +138,28 @@ def test_the_last_record_of_a_kind_holds(tmp_path):
     assert "clenshaw" in ctx.load_tuning(str(rec), "fp32", 24)
     assert ctx.launch_plan("fp32", "clenshaw", 24)["block"] == 64
     ctx.close()
+
+
+@pytest.mark.parametrize("prec,n", [("fp64", 3), ("fp32", 12), ("bf16", 24)])
+def test_autotune_keeps_the_rule_unless_a_shape_is_ahead(prec, n, tmp_path):
+    import json
+    L, path = (8, 8, 8, 16), tmp_path / "shapes.jsonl"
+    ctx = _ctx(L)
+    x = _x(L, n)
+    ref = ctx.dslash(x, prec=prec)
+    rule = {k: ctx.launch_plan(prec, k, n) for k in ("dslash", "clenshaw")}
+    ctx.autotune(prec, n, str(path))
+    recs = [json.loads(line) for line in path.read_text().splitlines()]
+    assert [r["kind"] for r in recs] == ["dslash", "clenshaw"]
+    plan = {k: ctx.launch_plan(prec, k, n) for k in rule}
+    for r in recs:
+        ahead = r["ms_per_launch"] / r["ms_unchosen"]   # the file rounds to a nanosecond
+        assert (r["chosen"] == 1 and ahead < 0.981) or (r["chosen"] == 0 and ahead > 0.979)
+        assert plan[r["kind"]]["chosen"] == bool(r["chosen"])
+        assert r["chosen"] or plan[r["kind"]] == rule[r["kind"]]
+    assert torch.equal(ctx.dslash(x, prec=prec), ref)
+    ctx.close()
+    ctx = _ctx(L)
+    assert ctx.load_tuning(str(path), prec, n) == ["dslash", "clenshaw"]
+    assert {k: ctx.launch_plan(prec, k, n) for k in rule} == plan
+    ctx.close()
