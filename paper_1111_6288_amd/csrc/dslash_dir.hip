@@ -346,13 +346,15 @@ hipError_t launch_dslash_dir(const DsArgs<S> &a, bool hw, bool epi, hipStream_t 
     const int ny = b.order != 0 ? (a.g.V / 8 + 63) / 64 : b.xcd_remap ? (nsb + 7) / 8 : nsb;
     if (!dslash_dir_fits(a.g) || a.n > (1 << 24) || (epi && a.yc)) return hipErrorInvalidValue;
     const dim3 grid(b.xcd_remap ? 8 * a.n : a.n, ny);
-    if (a.recon) {
-        if (a.stream_hint) launch_dir_kernel<S, true, true>(b, hw, epi, grid, st);
-        else launch_dir_kernel<S, true, false>(b, hw, epi, grid, st);
-    } else {
-        if (a.stream_hint) launch_dir_kernel<S, false, true>(b, hw, epi, grid, st);
-        else launch_dir_kernel<S, false, false>(b, hw, epi, grid, st);
-    }
+    // BF16 batches of this kernel are far smaller than the caches: they take no stream hint
+    auto launch = [&](auto rec) {
+        constexpr bool REC = decltype(rec)::value;
+        if constexpr (sizeof(S) != 4)
+            if (a.stream_hint) return launch_dir_kernel<S, REC, true>(b, hw, epi, grid, st);
+        launch_dir_kernel<S, REC, false>(b, hw, epi, grid, st);
+    };
+    if (a.recon) launch(std::true_type{});
+    else launch(std::false_type{});
     return hipGetLastError();
 }
 
