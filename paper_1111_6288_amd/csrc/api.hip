@@ -439,8 +439,8 @@ const uint32_t *links_of<uint32_t>(const ov_ctx *c) { return c->U16; }
 // ---------------------------------------------------------------- launch helpers
 // Kernel and shape of a dslash launch that nobody chose (ov_set_tuning and its relatives,
 // ov_autotune), by the bytes of one field batch F = 12 V n and the batch size n.  All kernels and
-// shapes give the same bits.  Times are the mean of a plain and a fused launch in a captured graph
-// (an empty node takes 1.6 us).
+// shapes give the same bits for a batch.  Times are the mean of a plain and a fused launch in a
+// captured graph (an empty node takes 1.6 us).
 //
 // Direction waves for small batches, which wait for memory latency, not bandwidth: FP64 12 RHS of
 // 4^4 16.7 (two RHS per thread) -> 4.7 us, FP32 4 RHS of 8^3x16 16.3 -> 6.1 us.  Every right-hand

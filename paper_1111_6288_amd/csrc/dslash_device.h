@@ -162,7 +162,11 @@ __device__ __forceinline__ void load_spinor(const S *__restrict__ x, int Vp, uns
 // spinor.  Which product of the imaginary part is rounded first is fixed per
 // storage type and component, so that all dslash kernels agree to the last
 // bit: the phase is the one FP32 factor of a BF16 hop whose products are not
-// exact.  `single`: the batch is one right-hand side.
+// exact.  The choice itself has no numerical reason: it keeps the results that
+// BF16 batches, and single BF16 vectors (`single`), had before the products
+// were written out, when the compiler chose for each kernel.  A BF16 vector
+// alone and in a batch therefore agree to BF16 rounding only; in FP64 and FP32
+// they are the same bits.
 template <class S, class R>
 __device__ __forceinline__ cx<R> phase_mul(cx<R> f, cx<R> h, int k, int c, bool single)
 {

@@ -30,7 +30,7 @@ template <class R>
 __device__ __forceinline__ cx<R> csub(cx<R> a, cx<R> b) { return {a.x - b.x, a.y - b.y}; }
 // Products name which of their two multiplications is fused into the sum, so
 // that every kernel rounds alike wherever the compiler finds them: the dslash
-// kernels give the same bits for every launch shape.
+// kernels give the same bits for every launch shape of a batch.
 // a * b
 template <class R>
 __device__ __forceinline__ cx<R> cmul(cx<R> a, cx<R> b)

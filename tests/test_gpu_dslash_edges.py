@@ -103,3 +103,37 @@ def test_bf16_storage_rounds_to_nearest_even(n):
         assert torch.equal(got.nan_to_num(0.0, float("inf"), float("-inf")),
                            want.nan_to_num(0.0, float("inf"), float("-inf")))
     ctx.close()
+
+
+@pytest.mark.parametrize("su3", [True, False])
+@pytest.mark.parametrize("L,bc", [((8, 8, 8, 16), (2, 1, 0, 2)), ((6, 5, 7, 10), (1, 2, 0, 1))])
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16"])
+def test_every_launch_shape_gives_the_bits_of_the_rule(L, bc, prec, su3):
+    """Plain and fused launches of a batch, whichever kernel and shape runs them; in FP64 and FP32 also a vector alone and
+    in a batch (BF16 rounds the phase of a single vector another way)."""
+    U = synth.su3_links(L, 0.4, 3)
+    if not su3:
+        U = U * np.exp(1j * np.random.default_rng(3).uniform(-1, 1, (4, synth.volume(L), 1, 1)))
+    ctx = _ctx(L, bc, np.ascontiguousarray(U))
+    ctx.set_sign_params(4, 0.02, 8.5)
+    gen = torch.Generator(device="cuda").manual_seed(2)
+    x = torch.randn((60, synth.volume(L), 4, 3), dtype=torch.complex128, device="cuda", generator=gen)
+    one = dict(rhs_split=1, wshare=1, site_order=0)
+    shapes = [dict(one, rhs_per_thread=nr, block=bl, site_order=o) for nr in (1, 2, 4, 8) for bl in (64, 256) for o in (0, 1, 3)]
+    shapes += [dict(one, rhs_per_thread=nr, block=128, rhs_split=q, wshare=w) for nr in (1, 2) for q in (1, 2, 4)
+               for w in (1, 2, 4, 8)]
+    shapes += [dict(one, rhs_per_thread=nr, block=128, rhs_split=8) for nr in (1, 2) if prec != "bf16"]
+    shapes += [dict(one, rhs_per_thread=1, block=bl, site_order=2) for bl in (256, 512)]
+
+    def run(n):
+        xs, f = x[:n].contiguous(), [j % 2 for j in range(n)]
+        return ctx.dslash(xs, f, prec=prec), ctx.dov_apply(xs, f, [0.1] * n, prec=prec)
+    ref = {n: run(n) for n in (1, 2, 5, 12, 60)}
+    if prec != "bf16":
+        assert all(torch.equal(r[0], ref[60][0][:n]) for n, r in ref.items())
+    for s in shapes:
+        for kind in ("dslash", "clenshaw"):
+            ctx.set_launch_config(prec, kind, **s)
+        for n, r in ref.items():
+            assert all(torch.equal(a, b) for a, b in zip(r, run(n))), (s, n)
+    ctx.close()
