@@ -85,6 +85,17 @@ __device__ __forceinline__ void add_shared_hop(const RawSpinor<S> &raw, const LF
 template <class S>
 constexpr int share_depth() { return sizeof(S) == 4 ? 1 : 2; }
 
+// Units of the own-site operands requested ahead in a fused launch.  FP64 has
+// two waves per SIMD and twice the units of FP32; loaded one unit after the
+// other, behind the stores, each cost a memory latency, and the kernel was
+// behind the one that it replaced, which runs three waves per SIMD.  Microseconds
+// per vector of a fused launch, 12 RHS on z-slabs with the stream hint, that
+// kernel / none ahead / three ahead: 24^3x48 147.2 / 151.5 / 145.4, 24^3x24 72.4 /
+// 75.5 / 71.9, 16^3x32 30.1 / 29.1 / 26.6, 32^3x32 246 / 244 / 236.  FP32 and BF16
+// hide it behind four waves and more.
+template <class S>
+constexpr int share_epilogue_depth() { return sizeof(S) == 16 ? 3 : 0; }
+
 // LDS of a wave for the canonical output: four components of 64 sites, rows of
 // five numbers (20 dwords: 16 lanes of a 16-byte access meet in no bank).
 constexpr int kCanonRow = 5, kCanonWave = 64 * kCanonRow;
@@ -198,14 +209,22 @@ __global__ __launch_bounds__(512, sizeof(S) == 16 ? 2 : 4) void k_dslash_share(D
     const R cc[3] = {(R)a.c1, (R)a.c2, (R)a.c3};
     const S *ep[3] = {a.e1, a.e2, a.e3};
     const unsigned ob = (unsigned)s0 * (unsigned)Raw::B;
-#pragma unroll
-    for (int q = 0; q < Raw::N; ++q) {
-        uint32_t er[3][Raw::B / 4];
+    // own-site operands, A units ahead of their use
+    constexpr int A = share_epilogue_depth<S>();
+    uint32_t eb[A + 1][3][Raw::B / 4];
+    auto operands = [&](int q) {
         if constexpr (EPI) {
 #pragma unroll
             for (int t = 0; t < 3; ++t)
-                if (ep[t]) Raw::template ld<NT ? 2 : 0>(ep[t] + off, g.Vp, q, ob, er[t]);
+                if (ep[t]) Raw::template ld<NT ? 2 : 0>(ep[t] + off, g.Vp, q, ob, eb[q % (A + 1)][t]);
         }
+    };
+#pragma unroll
+    for (int q = 0; q < A; ++q) operands(q);
+#pragma unroll
+    for (int q = 0; q < Raw::N; ++q) {
+        if (q + A < Raw::N) operands(q + A);
+        const auto &er = eb[q % (A + 1)];
         cx<R> v[Raw::C];
 #pragma unroll
         for (int h = 0; h < Raw::C; ++h) {
