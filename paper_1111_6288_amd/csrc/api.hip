@@ -1246,7 +1246,7 @@ int ov_upload_gauge(ov_ctx *c, const void *U_dev)
         CHK(dev_alloc(c, (void **)&c->U32, n * sizeof(float2)));
         CHK(dev_alloc(c, (void **)&c->U16, n * sizeof(uint32_t)));
     }
-    HIPCHK(launch_pack_links((const double2 *)U_dev, c->U64, c->U32, c->U16, c->g.V, c->g.Vp, c->stream));
+    HIPCHK(launch_pack_links((const double2 *)U_dev, c->U64, c->U32, c->U16, c->g, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
     std::memcpy(&c->row3_dev, &h.row3, sizeof(double));
     for (int p = 0; p < 2; ++p)

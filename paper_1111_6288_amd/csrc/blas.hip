@@ -126,21 +126,28 @@ __device__ __forceinline__ void wave_links(const double2 *__restrict__ U, int mu
     for (int k = 0; k < 9; ++k) m[k] = sh[wave][lane * 9 + k];
 }
 
-// canonical [4][V][3][3]  ->  the three internal link layouts, one direction per wave
+// canonical [4][V][3][3]  ->  the three internal link layouts, one direction per wave.  Links across a
+// Dirichlet boundary become zeros: no hop has them, whatever they hold (a finite FP64 number may
+// overflow the other layouts), and the kernels that do not branch on boundaries multiply a neighbour
+// of zeros by them.
 __global__ __launch_bounds__(256) void k_pack_links(const double2 *__restrict__ in, double2 *__restrict__ o64,
-                                                    float2 *__restrict__ o32, uint32_t *__restrict__ o16, int V, int Vp)
+                                                    float2 *__restrict__ o32, uint32_t *__restrict__ o16, Geo g)
 {
     __shared__ double2 sh[4][64 * 9];
     const int base = blockIdx.x * 64, mu = (int)(threadIdx.x >> 6);
-    const long site = base + (int)(threadIdx.x & 63);   // < Vp, a multiple of 64
+    const int s = base + (int)(threadIdx.x & 63);   // < Vp, a multiple of 64
+    const long site = s;
     double2 m[9];
-    wave_links(in, mu, base, V, sh, m);
+    wave_links(in, mu, base, g.V, sh, m);
+    const int step = mu == 0 ? 1 : mu == 1 ? g.Lx : mu == 2 ? g.Lxy : g.Lxyz;
+    const int L = mu == 0 ? g.Lx : mu == 1 ? g.Ly : mu == 2 ? g.Lz : g.Lt;
+    const bool open = g.bcf[mu] == 0.0f && s / step % L == L - 1;
 #pragma unroll
     for (int k = 0; k < 9; ++k) {
-        const cx<double> v = {m[k].x, m[k].y};
-        stc<double>(o64, lpos<double2>(mu, k, site, Vp), v);
-        stc<double>(o32, lpos<float2>(mu, k, site, Vp), v);
-        stc<double>(o16, lpos<uint32_t>(mu, k, site, Vp), v);
+        const cx<double> v = {open ? 0.0 : m[k].x, open ? 0.0 : m[k].y};
+        stc<double>(o64, lpos<double2>(mu, k, site, g.Vp), v);
+        stc<double>(o32, lpos<float2>(mu, k, site, g.Vp), v);
+        stc<double>(o16, lpos<uint32_t>(mu, k, site, g.Vp), v);
     }
 }
 
@@ -494,10 +501,10 @@ hipError_t launch_unpack_spinor(const S *in, double2 *out, long fstride, const i
     return hipGetLastError();
 }
 
-hipError_t launch_pack_links(const double2 *in, double2 *o64, float2 *o32, uint32_t *o16, int V, int Vp,
+hipError_t launch_pack_links(const double2 *in, double2 *o64, float2 *o32, uint32_t *o16, const Geo &g,
                              hipStream_t st)
 {
-    hipLaunchKernelGGL(k_pack_links, dim3(Vp / 64), dim3(256), 0, st, in, o64, o32, o16, V, Vp);
+    hipLaunchKernelGGL(k_pack_links, dim3(g.Vp / 64), dim3(256), 0, st, in, o64, o32, o16, g);
     return hipGetLastError();
 }
 

@@ -274,24 +274,20 @@ struct RawSpinor {
     }
 };
 
-// A byte offset beyond every plane, also when halved (planes of less than
-// 2^25 sites): a buffer load answers it with zeros.
-constexpr unsigned kBeyondPlane = 0x80000000u;
-
 // Byte offset inside a plane of the neighbour of site s0 (wrap: the hop
-// leaves the lattice; step +-stride, L the extent); beyond the plane across a
-// Dirichlet boundary.  Such a hop is dropped: neighbour and link both read as
-// zeros, since a link that nothing applies may hold any finite number, also
-// one that overflows the storage type.
+// leaves the lattice; step +-stride, L the extent); across a Dirichlet
+// boundary one beyond every plane, which a buffer load answers with zeros.
+// Zeros times the link are nothing only where the link is finite in the
+// storage type; links across such a boundary are packed as zeros.
 template <class S>
 __device__ __forceinline__ unsigned neighbour_offset(int s0, bool wrap, int L, int step, float bc)
 {
     const unsigned o = (unsigned)(wrap ? s0 - (L - 1) * step : s0 + step) * (unsigned)RawSpinor<S>::B;
-    return wrap && bc == 0.0f ? kBeyondPlane : o;
+    return wrap && bc == 0.0f ? 0x80000000u : o;
 }
 
 // Link of direction mu through plane resources; `e` is the site's byte offset
-// in a plane of elements of RawSpinor<S>::B bytes (beyond the plane: zeros).
+// in a plane of elements of RawSpinor<S>::B bytes.
 template <class S, bool REC>
 __device__ __forceinline__ void load_link_buf(const S *U, int mu, int Vp, unsigned e,
                                               cx<typename StoreT<S>::real> (&u)[3][3])
@@ -307,12 +303,7 @@ __device__ __forceinline__ void load_link_buf(const S *U, int mu, int Vp, unsign
         for (int h = 0; h < Raw::C; ++h) u[(q * Raw::C + h) / 3][(q * Raw::C + h) % 3] = Raw::get(o, h);
     }
     if constexpr (REC) rebuild_row2(u);
-    else if constexpr (Raw::C == 2) {   // component 8 has a plane of single numbers
-        const auto r = __builtin_amdgcn_make_buffer_rsrc((void *)(b + (size_t)8 * (unsigned)Vp), 0,
-                                                         (unsigned)Vp * (unsigned)sizeof(S), 0x00020000);
-        const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, e / 2, 0, 0);
-        u[2][2] = cmk(__uint_as_float(v[0]), __uint_as_float(v[1]));
-    }
+    else if constexpr (Raw::C == 2) u[2][2] = ldp<S, typename StoreT<S>::real>(b + (size_t)8 * (unsigned)Vp, e / Raw::B);
 }
 
 __device__ __forceinline__ float flip_sign(float v, uint32_t bit) { return __uint_as_float(__float_as_uint(v) ^ bit); }

@@ -80,13 +80,12 @@ __device__ __forceinline__ void dir_hops(const DsArgs<S> &a, const S *__restrict
     const int Vp = a.g.Vp;
     const float bc = a.g.bcf[MU];
     const bool wf = cmu == Lmu - 1, wb = cmu == 0;
-    // the link of a hop across a Dirichlet boundary reads as zeros like its neighbour
-    const unsigned es = wf && bc == 0.0f ? kBeyondPlane : (unsigned)site * (unsigned)Raw::B;
-    const unsigned eu = neighbour_offset<S>(site, wb, Lmu, -stride, bc);
+    const unsigned es = (unsigned)site * (unsigned)Raw::B;
+    const unsigned eu = (unsigned)(wb ? site + (Lmu - 1) * stride : site - stride) * (unsigned)Raw::B;
     cx<R> uf[3][3], ub[3][3], pf[4][3], pb[4][3];
     Raw rf, rb;
     if constexpr (HOPS & 1) rf.load(x, Vp, neighbour_offset<S>(site, wf, Lmu, stride, bc));
-    if constexpr (HOPS & 2) rb.load(x, Vp, eu);
+    if constexpr (HOPS & 2) rb.load(x, Vp, neighbour_offset<S>(site, wb, Lmu, -stride, bc));
     if constexpr (HOPS & 1) load_link_buf<S, REC>(a.U, MU, Vp, es, uf);
     if constexpr (HOPS & 2) load_link_buf<S, REC>(a.U, MU, Vp, eu, ub);
     cx<R> hf[2][3], hb[2][3];

@@ -11,9 +11,9 @@
 // vectors on 24^3x48: 3.4 GB at 5.9 TB/s, 1.8 GB of it neighbours read again),
 // BF16 the vector arithmetic.  So loads take their addresses from scalar
 // resources, boundaries cost no branch (the staged link holds the sign of an
-// antiperiodic hop or zeros across a Dirichlet boundary, whose neighbour is
-// fetched from beyond the plane, which reads as zero), and with straight code the next neighbours are
-// requested while one is worked on.  Mean of a plain and a fused launch of 12
+// antiperiodic hop; a Dirichlet neighbour is fetched from beyond the plane, which
+// reads as zero, and its link is packed as zeros), and with straight code the
+// next neighbours are requested while one is worked on.  Mean of a plain and a fused launch of 12
 // vectors against the kernel with a branch per hop and 64-bit lane addresses:
 //   16^3x32  FP64 304 -> 281 us, FP32 145 -> 133, BF16 97 -> 103 (5: 48 -> 41)
 //   24^3x48  FP64 1525 -> 1511,  FP32 731 -> 719, BF16 506 -> 468
@@ -129,26 +129,16 @@ __global__ __launch_bounds__(512, sizeof(S) == 16 ? 2 : 4) void k_dslash_share(D
     const int s0 = real ? site : 0;   // other lanes load site 0 and drop the result
     int xc, yc, zc, tc;
     site_coords(g, s0, xc, yc, zc, tc);
-    // A Dirichlet hop's link is fetched from beyond the plane like its neighbour: zeros, whatever it holds.  (FP64 8 RHS
-    // of 8^3x16: 13.3 us; zeros written over the staged link 15.0; g.bcf indexed by mu, a scalar load per slot, 14.5.)
     for (int slot = wave; slot < 8; slot += W) {
-        const int mu = slot & 3;
-        const int c = mu == 0 ? xc : mu == 1 ? yc : mu == 2 ? zc : tc;
-        const int L = mu == 0 ? g.Lx : mu == 1 ? g.Ly : mu == 2 ? g.Lz : g.Lt;
-        const int st = mu == 0 ? 1 : mu == 1 ? g.Lx : mu == 2 ? g.Lxy : g.Lxyz;
-        const float bc = mu == 0 ? g.bcf[0] : mu == 1 ? g.bcf[1] : mu == 2 ? g.bcf[2] : g.bcf[3];
-        const bool edge = c == (slot < 4 ? L - 1 : 0);
-        const unsigned eb = neighbour_offset<S>(s0, edge, L, -st, bc);
-        const unsigned ef = edge && bc == 0.0f ? kBeyondPlane : (unsigned)s0 * (unsigned)Raw::B;
-        cx<R> u[3][3];
-        load_link_buf<S, REC>(a.U, mu, g.Vp, slot < 4 ? ef : eb, u);
-        const uint32_t sign = edge && bc < 0.0f ? 0x80000000u : 0u;   // antiperiodic hops: the link carries the sign
         cx<R> *dst = lk + slot * E * SL + lane;
+        stage_link<S, R, REC, E, SL>(a, slot, s0, xc, yc, zc, tc, dst);
+        if constexpr (E == 9) {   // antiperiodic hops: the link carries the sign
+            const int mu = slot & 3;
+            const int c = mu == 0 ? xc : mu == 1 ? yc : mu == 2 ? zc : tc;
+            const int L = mu == 0 ? g.Lx : mu == 1 ? g.Ly : mu == 2 ? g.Lz : g.Lt;
+            if (g.bcf[mu] < 0 && c == (slot < 4 ? L - 1 : 0))
 #pragma unroll
-        for (int k = 0; k < E; ++k) {
-            cx<R> v = u[k / 3][k % 3];
-            if constexpr (E == 9) v = cmk(flip_sign(v.x, sign), flip_sign(v.y, sign));
-            dst[k * SL] = v;
+                for (int k = 0; k < 9; ++k) dst[k * SL] = cmk(-dst[k * SL].x, -dst[k * SL].y);
         }
     }
 

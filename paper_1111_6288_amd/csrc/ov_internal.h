@@ -92,8 +92,8 @@ hipError_t launch_pack_spinor(const double2 *in, S *out, long fstride, const int
 template <class S>
 hipError_t launch_unpack_spinor(const S *in, double2 *out, long fstride, const int *slots, int n, int V, int Vp,
                                 hipStream_t st);
-// canonical [4][V][3][3] to the three link layouts
-hipError_t launch_pack_links(const double2 *in, double2 *o64, float2 *o32, uint32_t *o16, int V, int Vp,
+// canonical [4][V][3][3] to the three link layouts; links across a Dirichlet boundary as zeros
+hipError_t launch_pack_links(const double2 *in, double2 *o64, float2 *o32, uint32_t *o16, const Geo &g,
                              hipStream_t st);
 hipError_t launch_count_nonfinite(const double *p, long n, int *count, hipStream_t st);
 // What ov_upload_gauge asks of a field of links; maxima as the bits of
