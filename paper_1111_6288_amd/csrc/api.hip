@@ -443,29 +443,34 @@ const uint32_t *links_of<uint32_t>(const ov_ctx *c) { return c->U16; }
 // captured graph (an empty node takes 1.6 us).
 //
 // Direction waves for small batches, which wait for memory latency, not bandwidth: FP64 12 RHS of
-// 4^4 16.7 (two RHS per thread) -> 4.7 us, FP32 4 RHS of 8^3x16 16.3 -> 6.1 us.  Every right-hand
+// 4^4 16.7 (two RHS per thread) -> 4.5 us, FP32 4 RHS of 8^3x16 16.3 -> 5.9 us.  Every right-hand
 // side reads all eight links and rebuilds their third rows, so sharing staged links wins once the
-// fields outgrow the caches or, in FP64, the batch is long.  Direction waves (four
-// per block; eight, which such batches get, take up to 8 % less, 0.3 % at 12 RHS of 12^3x24) / shared links:
-//   FP64 6x5x7x10 12 RHS (5 MB) 8.7 / 12.2 us, 12^3x24 6 RHS (48 MB) 43.7 / 46.0, 8 RHS 58.8 / 59.8, 12 RHS (96 MB) 94 / 88,
-//        8^3x16 8 RHS 14.3 / 14.1, 24 RHS (38 MB) 35.7 / 33.0, 16^3x32 2 RHS 49 / 49, 4 RHS 102 / 95;
-//   FP32 12^3x24 8 RHS (32 MB) 28.3 / 29.6, 12 RHS (48 MB) 41.1 / 40.2, 16^3x32 6 RHS (75 MB) 77 / 69;
-//   BF16 12^3x24 3 RHS (6 MB) 12.7 / 14.2, 4 RHS (8 MB) 16.0 / 15.3, 16^3x32 2 RHS (13 MB) 22.9 / 25.7.
-// One or two vectors gain on the largest lattice too (one of 24^3x48: FP64 222 -> 157 us, FP32
-// 96 -> 70), except in BF16 (one thread for both 48 us, direction waves 56).
+// fields outgrow the caches or, in FP64, the batch is long.  Direction waves (eight per workgroup) /
+// shared links, us:
+//   FP64 6x5x7x10 12 RHS (5 MB) 7.9 / 10.8, 8^3x16 8 RHS (13 MB) 13.0 / 13.4, 24 RHS (38 MB) 34.9 / 34.3,
+//        12^3x24 4 RHS (32 MB) 29.2 / 31.2, 7 RHS (56 MB) 48.8 / 51.4, 8 RHS (64 MB) 57.7 / 58.7, 12 RHS (96 MB) 94 / 84,
+//        16^3x32 2 RHS (50 MB) 47.0 / 49.1, 3 RHS (75 MB) 76.1 / 71.4;
+//   FP32 12^3x24 10 RHS (40 MB) 34.2 / 36.8, 12 RHS (48 MB) 40.4 / 39.8, 16^3x32 3 RHS (38 MB) 33.7 / 34.0,
+//        4 RHS (50 MB) 43.3 / 41.5, 6 RHS (75 MB) 78 / 70;
+//   BF16 12^3x24 3 RHS (6 MB) 11.2 / 14.6, 4 RHS (8 MB) 14.0 / 15.2, 6 RHS (12 MB) 19.1 / 18.5, 16^3x32 2 RHS (13 MB)
+//        20.0 / 28.0.
+// (The FP64 limit of 7 and the BF16 one of 7 MB were drawn with four waves; eight are still ahead, by
+// 2 to 8 %, in the next sizes, FP64 8 RHS and BF16 up to 10 MB.)  One or two vectors gain on the largest
+// lattice too (one of 24^3x48, four waves: FP64 222 -> 151 us, FP32 96 -> 78, with the hint 70), except
+// in BF16 (one thread for both 45 us, direction waves 48).
 //
 // Link sharing: the W waves of a workgroup hold W right-hand sides of the same sites.  W = 8, or the
 // even split of a batch that would leave more than half of a workgroup idle (24^3x48 FP32: 12 RHS
-// W 8 719 us, W 6 739, W 4 754, two RHS per thread 1121; 9 RHS W 8 623, W 5 560; BF16 12 RHS W 8
-// 470, W 4 490, two per thread 554).  FP64 stages twice the bytes: W up to 4, split evenly (12 RHS
-// W 4 1511, W 8 1607, two per thread 2459; 5 RHS W 3 681, W 4 734).
+// W 8 710 us, W 6 725, W 4 747, two RHS per thread 1121; 9 RHS W 8 571, W 5 552; BF16 12 RHS W 8
+// 454, W 4 481, two per thread 554).  FP64 stages twice the bytes: W up to 4, split evenly (12 RHS
+// W 4 1473, W 6 1512, W 8 1530, two per thread 2459; 5 RHS W 3 645, W 4 662).
 //
 // Site order and streams: large batches walk z-slabs per XCD (t-slabs where Lz % 8) with
-// non-temporal own-site streams (24^3x48 FP64 one vector: canonical order 175, z-slabs 164, with
-// the hint 157; 16^3x32 FP32 8 RHS, 100 MB: t-slabs 96.8, z-slabs with the hint 91.6).  What the
-// caches still hold between launches takes t-slabs without the hint (16^3x32 FP64 one vector
-// 31.2 -> 28.4, with the hint 31.0; FP32 6 RHS, 75 MB, 70.6 against 73.5), BF16 canonical order
-// (16^3x32 12 RHS 92 us, z-slabs with the hint 103).
+// non-temporal own-site streams (24^3x48 FP64 one vector: canonical order 172, z-slabs 162, with
+// the hint 151; 16^3x32 FP32 8 RHS, 100 MB: t-slabs 95.8, z-slabs with the hint 91.0).  What the
+// caches still hold between launches takes t-slabs without the hint (16^3x32 FP64 one vector:
+// canonical 29.3, t-slabs 26.6, with the hint 28.6; FP32 6 RHS, 75 MB, 70.2 against 72.6), BF16
+// canonical order (16^3x32 12 RHS 91 us, z-slabs with the hint 101).
 template <class S>
 ov_ctx::Launch launch_rule(const Geo &g, int n)
 {

@@ -18,8 +18,8 @@
 // in turn.  It also has eight times the wavefronts for the same sites.
 // Mean of a plain and a fused launch in a captured graph (an empty node takes
 // 1.6 us), site-parallel kernel and this one:
-//   FP64 12 RHS of 4^4 16.7 -> 4.7 us, FP32 4 RHS of 8^3x16 16.3 -> 6.1 us,
-//   FP64 1 RHS of 16^3x32 37.7 -> 27 us, of 24^3x48 222 -> 157 us.
+//   FP64 12 RHS of 4^4 16.7 -> 4.5 us, FP32 4 RHS of 8^3x16 16.3 -> 5.9 us,
+//   FP64 1 RHS of 16^3x32 37.7 -> 27 us, of 24^3x48 222 -> 151 us.
 // Loading every argument at once at the top instead of where it is needed, and slots and field
 // groups as arguments instead of lists, gained nothing (1.00x; the latter 0.94x on 4^4).
 #include <type_traits>
@@ -169,8 +169,8 @@ __device__ __forceinline__ cx<R> sum_hops(const cx<R> *__restrict__ g)
 // in the LDS of the hops, which have been summed by then) instead of a field.
 //
 // dir_waves: eight waves, one hop each, have half the loads and arithmetic of a
-// hop pair in a row; four waves are fewer to start and to meet at the barrier.  Mean of
-// a plain and a fused launch, four / eight waves:
+// hop pair in a row; four waves are fewer to start and to meet at the barrier.
+// Mean of a plain and a fused launch, four / eight waves:
 //   FP64 12 RHS of 4^4 5.0 / 4.7 us, FP32 5 RHS of 6x5x7x10 4.8 / 4.4, FP32 4 RHS of 8^3x16 6.5 / 6.1,
 //   FP64 4 RHS of 8^3x16 8.7 / 8.2, of 12^3x24 32.1 / 29.4, FP64 1 RHS of 16^3x32 28.9 / 27.3,
 // but in batches that stream past the caches four read less again:

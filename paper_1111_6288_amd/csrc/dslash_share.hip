@@ -13,10 +13,12 @@
 // resources, boundaries cost no branch (the staged link holds the sign of an
 // antiperiodic hop; a Dirichlet neighbour is fetched from beyond the plane, which
 // reads as zero, and its link is packed as zeros), and with straight code the
-// next neighbours are requested while one is worked on.  Mean of a plain and a fused launch of 12
-// vectors against the kernel with a branch per hop and 64-bit lane addresses:
-//   16^3x32  FP64 304 -> 281 us, FP32 145 -> 133, BF16 97 -> 103 (5: 48 -> 41)
-//   24^3x48  FP64 1525 -> 1511,  FP32 731 -> 719, BF16 506 -> 468
+// next neighbours are requested while one is worked on.  Mean of a plain and a
+// fused launch of 12 vectors against the kernel with a branch per hop and 64-bit
+// lane addresses, same shape (FP64 W 4, else W 8; z-slabs with the stream hint):
+//   16^3x32  FP64 303 -> 264 us, FP32 146 -> 132, BF16 98 -> 101
+//   24^3x48  FP64 1502 -> 1473,  FP32 727 -> 702, BF16 507 -> 456
+// BF16 takes canonical order on 16^3x32, where that is 96 -> 91 (5 vectors 45 -> 39).
 // Fewer workgroups per CU cut the traffic (two of six waves: 2.6 GB) but leave
 // too few loads in flight to gain from it.
 #include <type_traits>
@@ -81,7 +83,7 @@ __device__ __forceinline__ void add_shared_hop(const RawSpinor<S> &raw, const LF
 // Neighbours requested ahead.  Two fill the registers of four waves per SIMD
 // (FP64: two); BF16 spends its time on arithmetic and does better with more
 // waves (24^3x48, 12 RHS, one / two ahead: FP32 770 / 719 us, FP64 1530 / 1511,
-// BF16 470 / 494).
+// both before the epilogue below, BF16 470 / 494).
 template <class S>
 constexpr int share_depth() { return sizeof(S) == 4 ? 1 : 2; }
 

@@ -269,8 +269,8 @@ __global__ __launch_bounds__(256, 3) void k_proj_dot_mfma_pair(const double2 *__
 }
 
 // C[e] = sum_c part[c][e], e = (j, i), added in the order of the K-chunks.  A workgroup of 256 threads
-// owns kRedE consecutive e: all threads fetch the partials of 256 chunks into LDS (16 consecutive e are
-// 256 bytes of a row of part), then thread (e, component) adds them in order from there, while the next
+// owns kRedE consecutive e: all threads fetch the partials of 256 chunks into LDS (four consecutive e are
+// 64 bytes of a row of part), then thread (e, component) adds them in order from there, while the next
 // 256 are on their way.  One thread per e, walking memory by itself, waits for a load every few
 // additions and leaves all but a few CUs idle.
 constexpr int kRedE = 4, kRedC = 256;   // a row of partials in LDS is padded by one element
