@@ -447,9 +447,9 @@ const uint32_t *links_of<uint32_t>(const ov_ctx *c) { return c->U16; }
 // side reads all eight links and rebuilds their third rows, so sharing staged links wins once the
 // fields outgrow the caches or, in FP64, the batch is long.  Direction waves (eight per workgroup) /
 // shared links, us:
-//   FP64 6x5x7x10 12 RHS (5 MB) 7.9 / 10.8, 8^3x16 8 RHS (13 MB) 13.0 / 13.4, 24 RHS (38 MB) 34.9 / 34.3,
-//        12^3x24 4 RHS (32 MB) 29.2 / 31.2, 7 RHS (56 MB) 48.8 / 51.4, 8 RHS (64 MB) 57.7 / 58.7, 12 RHS (96 MB) 94 / 84,
-//        16^3x32 2 RHS (50 MB) 47.0 / 49.1, 3 RHS (75 MB) 76.1 / 71.4;
+//   FP64 6x5x7x10 12 RHS (5 MB) 7.9 / 10.3, 8^3x16 8 RHS (13 MB) 13.0 / 13.3, 24 RHS (38 MB) 34.7 / 32.8,
+//        12^3x24 4 RHS (32 MB) 29.2 / 31.2, 7 RHS (56 MB) 48.7 / 51.7, 8 RHS (64 MB) 57.9 / 59.1, 12 RHS (96 MB) 94 / 83,
+//        16^3x32 2 RHS (50 MB) 47.4 / 49.5, 3 RHS (75 MB) 76.1 / 71.1;
 //   FP32 12^3x24 10 RHS (40 MB) 34.2 / 36.8, 12 RHS (48 MB) 40.4 / 39.8, 16^3x32 3 RHS (38 MB) 33.7 / 34.0,
 //        4 RHS (50 MB) 43.3 / 41.5, 6 RHS (75 MB) 78 / 70;
 //   BF16 12^3x24 3 RHS (6 MB) 11.2 / 14.6, 4 RHS (8 MB) 14.0 / 15.2, 6 RHS (12 MB) 19.1 / 18.5, 16^3x32 2 RHS (13 MB)
@@ -463,7 +463,7 @@ const uint32_t *links_of<uint32_t>(const ov_ctx *c) { return c->U16; }
 // even split of a batch that would leave more than half of a workgroup idle (24^3x48 FP32: 12 RHS
 // W 8 710 us, W 6 725, W 4 747, two RHS per thread 1121; 9 RHS W 8 571, W 5 552; BF16 12 RHS W 8
 // 454, W 4 481, two per thread 554).  FP64 stages twice the bytes: W up to 4, split evenly (12 RHS
-// W 4 1473, W 6 1512, W 8 1530, two per thread 2459; 5 RHS W 3 645, W 4 662).
+// W 4 1462, W 6 1504, W 8 1522, two per thread 2459; 5 RHS W 3 642, W 4 656).
 //
 // Site order and streams: large batches walk z-slabs per XCD (t-slabs where Lz % 8) with
 // non-temporal own-site streams (24^3x48 FP64 one vector: canonical order 172, z-slabs 162, with

@@ -17,7 +17,7 @@
 // fused launch of 12 vectors against the kernel with a branch per hop and 64-bit
 // lane addresses, same shape (FP64 W 4, else W 8; z-slabs with the stream hint):
 //   16^3x32  FP64 303 -> 264 us, FP32 146 -> 132, BF16 98 -> 101
-//   24^3x48  FP64 1502 -> 1473,  FP32 727 -> 702, BF16 507 -> 456
+//   24^3x48  FP64 1502 -> 1461,  FP32 727 -> 702, BF16 507 -> 456
 // BF16 takes canonical order on 16^3x32, where that is 96 -> 91 (5 vectors 45 -> 39).
 // Fewer workgroups per CU cut the traffic (two of six waves: 2.6 GB) but leave
 // too few loads in flight to gain from it.
@@ -92,11 +92,13 @@ constexpr int share_depth() { return sizeof(S) == 4 ? 1 : 2; }
 // other, behind the stores, each cost a memory latency, and the kernel was
 // behind the one that it replaced, which runs three waves per SIMD.  Microseconds
 // per vector of a fused launch, 12 RHS on z-slabs with the stream hint, that
-// kernel / none ahead / three ahead: 24^3x48 147.2 / 151.5 / 145.4, 24^3x24 72.4 /
-// 75.5 / 71.9, 16^3x32 30.1 / 29.1 / 26.6, 32^3x32 246 / 244 / 236.  FP32 and BF16
-// hide it behind four waves and more.
+// kernel / none ahead / six ahead: 24^3x48 147.8 / 149.5 / 143.4, 24^3x24 72.6 /
+// 75.9 / 71.5, 16^3x32 30.2 / 29.1 / 26.5, 32^3x32 247 / 244 / 239.  Small lattices
+// lose nothing with six, 1 % with two or three in places (mean of a step, 24 RHS of
+// 8^3x16, none / two / three / six: 33.6 / 34.4 / 33.9 / 32.7).  FP32 and BF16 hide
+// it behind four waves and more.
 template <class S>
-constexpr int share_epilogue_depth() { return sizeof(S) == 16 ? 3 : 0; }
+constexpr int share_epilogue_depth() { return sizeof(S) == 16 ? 6 : 0; }
 
 // LDS of a wave for the canonical output: four components of 64 sites, rows of
 // five numbers (20 dwords: 16 lanes of a 16-byte access meet in no bank).
